@@ -403,11 +403,12 @@ int sphx_gnn_train_step(sphx_ctx* ctx, double lr, double* loss);
 
 /* Per-launch device time (ms, HIP events over `reps` launches) of the
  * surrogate's kernels on the current configuration; ms has 7 entries:
- * ms[0] one fused message-passing layer (edge encoder, edge product,
- * messages and their sums in one kernel, no edge array in device memory),
- * ms[1] the graph's edge features, ms[2] the node update product, ms[3] one
- * whole forward pass as inference runs it (graph and features included, one
- * host synchronisation per pass); for comparison the same with the edge
+ * ms[0] one fused message-passing layer (edge features and encoder, edge
+ * product, messages and their sums, node update and the next layer's node
+ * products in one kernel, no edge array in device memory),
+ * ms[1] the training graph's edge features, ms[2] the node update product by
+ * itself, ms[3] one whole forward pass as inference runs it (features
+ * included); for comparison the same with the edge
  * activations through device memory (the training forward's form): ms[4]
  * the whole pass, ms[5] its edge product R = E0 Wc, ms[6] its message sums
  * of one layer. sizes (may be NULL): [0] node rows, [1] edges. */

@@ -43,6 +43,16 @@ __device__ __forceinline__ uint32_t bf16_bits(float x)
     return u >> 16;
 }
 
+// The same for two floats in one instruction (v_cvt_pk_bf16_f32): lo in the
+// low half. The bit arithmetic above costs nine.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t bf16_pair(float lo, float hi)
+{
+    const bf16x2 b = __builtin_convertvector(f32x2{lo, hi}, bf16x2);
+    return __builtin_bit_cast(uint32_t, b);
+}
+
 union Frag {
     bf16x8 v;
     uint32_t u[4];
@@ -56,10 +66,10 @@ __device__ __forceinline__ bf16x8 frag_from_f32(const float* p, bool ok)
     if (ok) {
         const float4 a = *(const float4*)p;
         const float4 b = *(const float4*)(p + 4);
-        f.u[0] = bf16_bits(a.x) | (bf16_bits(a.y) << 16);
-        f.u[1] = bf16_bits(a.z) | (bf16_bits(a.w) << 16);
-        f.u[2] = bf16_bits(b.x) | (bf16_bits(b.y) << 16);
-        f.u[3] = bf16_bits(b.z) | (bf16_bits(b.w) << 16);
+        f.u[0] = bf16_pair(a.x, a.y);
+        f.u[1] = bf16_pair(a.z, a.w);
+        f.u[2] = bf16_pair(b.x, b.y);
+        f.u[3] = bf16_pair(b.z, b.w);
     } else {
         f.q = make_uint4(0u, 0u, 0u, 0u);
     }
@@ -357,122 +367,386 @@ __global__ __launch_bounds__(256) void k_gnn_msg(int N, const int32_t* __restric
     X[(size_t)i * 2 * HID + HID + f] = acc;
 }
 
-// One message-passing layer for inference, fused: for every node i, over
-// its edges e in CSR order,
-//   E0_e = relu(G_e We + be),  R_e = E0_e Wc,
-//   m_e  = relu((P_i + (Q_j | qw)) + R_e),  A_i = sum_e m_e -> X[i][64 + f],
-// with the edge encoder and the edge product on the matrix cores, so that
-// neither E0 nor R nor the messages leave the wavefront (no E x 64 array in
-// HBM). Each wavefront takes NPW consecutive nodes and their edges in tiles
-// of 16. The products are computed transposed (features as MFMA rows, the
-// 16 edges as columns: A = W^T, B = the edge rows), so that each lane then
-// holds four consecutive features of one edge and gathers P_i and Q_j with
-// 16-byte loads. E0 goes from the accumulator layout to the operand layout
-// through LDS, rounded to bf16 as every product operand is; the messages go
-// through LDS to one lane per feature, which sums them per node in CSR
-// order. G rows hold the EFEAT edge features (the encoder's other inputs
-// are zero).
-template <int NPW>
-__global__ __launch_bounds__(256) void k_gnn_layer_fused(
-    int N, const int32_t* __restrict__ eoff, const int32_t* __restrict__ edst, const int32_t* __restrict__ esrc,
-    const float* __restrict__ G, const uint16_t* __restrict__ WeT, const float* __restrict__ be,
-    const uint16_t* __restrict__ WcT, const float* __restrict__ Pm, const float* __restrict__ Qm,
-    const float* __restrict__ qw, float* __restrict__ X)
+// Constants of a case's features.
+struct FeatScale {
+    float inv_u, inv_h, gx, gy, inv_pscale, c2, rho0;
+};
+template <typename real>
+__device__ __forceinline__ FeatScale feat_scale(const KP<real>& P)
 {
-    __shared__ __align__(16) uint16_t Es[4][16][HID + 8];
-    __shared__ __align__(16) float Ms[4][16][HID + 4];
+    FeatScale c;
+    c.inv_u = (float)(1.0 / P.u_ref);
+    c.inv_h = (float)P.inv_h;
+    c.gx = (float)P.g[0];
+    c.gy = (float)P.g[1];
+    const float gmag = sqrtf(c.gx * c.gx + c.gy * c.gy + (float)P.g[2] * (float)P.g[2]);
+    c.inv_pscale = 1.f / ((float)P.rho0 * gmag) * c.inv_h;
+    c.c2 = (float)P.c2;
+    c.rho0 = (float)P.rho0;
+    return c;
+}
+
+// The EFEAT features of one edge (x_j - x_i = -(dx, dy)).
+__device__ __forceinline__ void edge_features(const FeatScale& c, float dx, float dy, float dvx, float dvy, float wall,
+                                              float dpres, float f[EFEAT])
+{
+    const float rr = sqrtf(dx * dx + dy * dy);
+    f[0] = -dx * c.inv_h;
+    f[1] = -dy * c.inv_h;
+    f[2] = rr * c.inv_h;
+    f[3] = dvx * c.inv_u;
+    f[4] = dvy * c.inv_u;
+    f[5] = wendland_ratio(rr * c.inv_h);
+    f[6] = wall;
+    f[7] = dpres * c.inv_pscale;
+}
+
+// Inference runs the network in four launches, straight from the neighbour
+// lists: the node encoder (with layer 0's P and Q) and one kernel per layer
+// (with the next layer's P and Q, or the decoder). Nothing per edge reaches
+// HBM, and no edge count is needed on the host. Every value is rounded where
+// and summed in the order in which the separate products and sums of the
+// training path round and sum it, so the predictions agree bit for bit.
+
+// Rows N and N + 1 of a Q array: the learned vector that stands for Q_j at a
+// wall edge, and one so negative that its message is 0 (a tile row without an
+// edge). Edges then differ only in the row they read.
+__device__ __forceinline__ void special_rows(float* __restrict__ Q, int N, const float* __restrict__ qw)
+{
+    if (blockIdx.x != 0 || threadIdx.x >= HID) return;
+    Q[(size_t)N * HID + threadIdx.x] = qw[threadIdx.x];
+    Q[(size_t)(N + 1) * HID + threadIdx.x] = -3e38f;
+}
+
+// Node encoder H = relu(F Wn + bn), P = H Wa + bm, Q = H Wb of 16 nodes per
+// wavefront; the features are taken from the particle state in registers
+// (only lanes with g = 0 hold nonzero inputs).
+template <typename real>
+__global__ __launch_bounds__(256) void k_gnn_encode(
+    const KP<real>* __restrict__ Pt, const int32_t* __restrict__ tcase, int N, const int32_t* __restrict__ ncnt,
+    const int32_t* __restrict__ wcnt, const R4<real>* __restrict__ st, const uint16_t* __restrict__ WnT,
+    const float* __restrict__ bn, const uint16_t* __restrict__ WaT, const float* __restrict__ bm,
+    const uint16_t* __restrict__ WbT, const float* __restrict__ qw, float* __restrict__ H, float* __restrict__ Pm,
+    float* __restrict__ Qm)
+{
+    special_rows(Qm, N, qw);
+    __shared__ __align__(16) uint16_t Hs[4][16][HID + 8];
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int r = lane & 15, g = lane >> 4;
-    const int n0 = (blockIdx.x * 4 + wv) * NPW;
-    if (n0 >= N) return;
-    const int n1 = min(n0 + NPW, N);
-    const int e_beg = eoff[n0], e_end = eoff[n1];
+    const int m0 = (blockIdx.x * 4 + wv) * 16;
+    if (m0 >= N) return;  // N is a multiple of TILE: whole groups of 16 nodes
+    const KP<real>& P = Pt[tcase[m0 / TILE]];
+    const int i = m0 + r;
+    Frag f;
+    f.q = make_uint4(0u, 0u, 0u, 0u);
+    if (g == 0 && i < P.fbase + P.nf) {
+        const float inv_u = (float)(1.0 / P.u_ref);
+        const R4<real> si = st[i];
+        f.u[0] = bf16_pair((float)si.x * inv_u, (float)si.y * inv_u);
+        f.u[1] = bf16_pair((float)si.z / (0.01f * (float)P.rho0), (float)ncnt[i] / 32.f);
+        f.u[2] = bf16_pair((float)wcnt[i] / 16.f, 0.f);
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const bf16x8 w = frag_from_bf16(WnT + (size_t)(16 * t + r) * FPAD + 8 * g);
+        const f32x4 a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.v, w, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        const float bv = bn[16 * t + r];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float h = fmaxf(a[q] + bv, 0.f);
+            H[(size_t)(m0 + 4 * g + q) * HID + 16 * t + r] = h;
+            Hs[wv][4 * g + q][16 * t + r] = (uint16_t)bf16_pair(h, 0.f);
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const bf16x8 h0 = frag_from_bf16(&Hs[wv][r][8 * g]), h1 = frag_from_bf16(&Hs[wv][r][32 + 8 * g]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        f32x4 p = f32x4{0.f, 0.f, 0.f, 0.f}, q = p;
+        const uint16_t* wa = WaT + (size_t)(16 * t + r) * HID + 8 * g;
+        const uint16_t* wb = WbT + (size_t)(16 * t + r) * HID + 8 * g;
+        p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h0, frag_from_bf16(wa), p, 0, 0, 0);
+        q = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h0, frag_from_bf16(wb), q, 0, 0, 0);
+        p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h1, frag_from_bf16(wa + 32), p, 0, 0, 0);
+        q = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h1, frag_from_bf16(wb + 32), q, 0, 0, 0);
+        const float bv = bm[16 * t + r];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            Pm[(size_t)(m0 + 4 * g + k) * HID + 16 * t + r] = p[k] + bv;
+            Qm[(size_t)(m0 + 4 * g + k) * HID + 16 * t + r] = q[k] + 0.f;
+        }
+    }
+}
+
+// Weights of one layer kernel (bf16 matrices transposed, 64 x K) and of what
+// follows it: the next layer's P and Q, or (WaT null) the decoder.
+struct LayerW {
+    const uint16_t *WeT, *WcT, *WuT, *WaT, *WbT, *Wo1T;
+    const float *be, *bu, *bm, *qn, *bo1, *Wo2, *bo2;  // qn: the next layer's wall vector
+};
+
+// One message-passing layer over the neighbour lists: for every node i, over
+// its edges e (inner, then contact entries, in list order),
+//   E0_e = relu(G_e We + be),  R_e = E0_e Wc,
+//   m_e  = relu((P_i + (Q_j | qw)) + R_e),  A_i = sum_e m_e,
+//   H_i <- H_i + relu([H_i | A_i] Wu + bu),
+// then P, Q of the next layer (Q into the other buffer: this layer's is still
+// gathered by other blocks) or the decoder's outputs Y.
+//
+// A block takes 4 NPW consecutive nodes, a wavefront NPW of them. Edge
+// features are computed one edge per lane, 64 at a time, into LDS; the edge
+// products run on the matrix cores in tiles of 16 edges, transposed
+// (features as rows, edges as columns), and go through LDS to one lane per
+// feature. There the message needs Q_j as one 256-byte row at an address that
+// is uniform over the wavefront, and P_i stays in a register for a whole
+// node; 16 row loads are in flight while the tile's products run. (Gathering
+// P_i and Q_j in the matrix layout instead, with 16 bytes per lane, a row
+// offset load per node and a stored 32-byte feature row per edge, took 597 us
+// a layer and 398 us of features at 410k nodes and 8.1M edges.) The rows are
+// read with buffer loads, whose row offset is one lane read: addresses and
+// tests in the scalar unit cost as much issue time as the arithmetic
+// (173 scalar instructions a tile, 553 us). The node
+// update follows in the same block, on the rows it holds: wavefront w
+// computes output columns 16 w .. 16 w + 15.
+template <typename real, int NPW>
+__global__ __launch_bounds__(256, 4) void k_gnn_layer(
+    const KP<real>* __restrict__ Pt, const int32_t* __restrict__ tcase, int N, int lt,
+    const uint32_t* __restrict__ nbr, const int32_t* __restrict__ ncnt, const uint32_t* __restrict__ wnb,
+    const int32_t* __restrict__ wcnt, const R2<real>* __restrict__ geo, const R2<real>* __restrict__ wgeo,
+    const R4<real>* __restrict__ st, LayerW W, float* H, float* Pm, const float* __restrict__ Qm,
+    float* __restrict__ Qn, float* __restrict__ Y)
+{
+    constexpr int NB = 4 * NPW;   // nodes per block
+    constexpr int RT = NB / 16;   // row tiles of the node update
+    static_assert(NB % 16 == 0 && TILE % NB == 0 && NPW < 64, "whole row tiles inside one case");
+    __shared__ __align__(16) uint32_t Gs[4][64][4];
+    __shared__ __align__(16) uint16_t Es[4][16][HID + 8];
+    __shared__ __align__(16) float Ms[4][16][HID + 4];
+    __shared__ __align__(16) uint16_t As[NB][HID + 8];
+    __shared__ __align__(16) uint16_t Hb[NB][HID + 8];
+    static_assert(sizeof(Ms) >= sizeof(float) * NB * (HID + 4), "the decoder's rows reuse Ms");
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int r = lane & 15, g = lane >> 4;
+    const int nb0 = blockIdx.x * NB;   // N is a multiple of TILE, so every node exists
+    const int n0 = nb0 + wv * NPW;
+    const KP<real>& P = Pt[tcase[nb0 / TILE]];
+    if (W.WaT) special_rows(Qn, N, W.qn);
+    const __amdgpu_buffer_rsrc_t qrow =
+        __builtin_amdgcn_make_buffer_rsrc((void*)Qm, 0, (int)((unsigned)(N + 2) * HID * sizeof(float)), 0x00020000);
+    const FeatScale fs = feat_scale(P);
+    const int maxn = P.maxn, maxw = P.maxw;
+    const real L0 = P.L[0], L1 = P.L[1];
+    // lane p < NPW: inner count and (scanned) first edge of node n0 + p
+    int nin = 0, tot = 0;
+    if (lane < NPW && n0 + lane < P.fbase + P.nf) {
+        nin = ncnt[n0 + lane];
+        tot = nin + wcnt[n0 + lane];
+    }
+    int off = tot;
+#pragma unroll
+    for (int o = 1; o < NPW; o <<= 1) {
+        const int a = __shfl_up(off, o);
+        if (lane >= o) off += a;
+    }
+    const int ne = __builtin_amdgcn_readlane(off, NPW - 1);
+    off -= tot;
     // weight fragments and the encoder bias of this lane, kept for all tiles
     bf16x8 wef[4], wcf[2][4];
     float bev[4][4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-        wef[t] = frag_from_bf16(WeT + (size_t)(16 * t + r) * FPAD + 8 * g);
+        wef[t] = frag_from_bf16(W.WeT + (size_t)(16 * t + r) * FPAD + 8 * g);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) wcf[k][t] = frag_from_bf16(WcT + (size_t)(16 * t + r) * HID + 32 * k + 8 * g);
+        for (int k = 0; k < 2; ++k) wcf[k][t] = frag_from_bf16(W.WcT + (size_t)(16 * t + r) * HID + 32 * k + 8 * g);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) bev[t][q] = be[16 * t + 4 * g + q];
+        for (int q = 0; q < 4; ++q) bev[t][q] = W.be[16 * t + 4 * g + q];
     }
     // the reduction: lane = feature, running node `cur` (uniform)
-    int cur = n0;
-    int cend = eoff[n0 + 1];
+    int cur = 0;
     float sum = 0.f;
-    for (int eb = e_beg; eb < e_end; eb += 16) {
-        const int e = eb + r;
-        const bool ok = e < e_end;
-        const int src = ok ? esrc[e] : n0;
-        const int dst = ok ? edst[e] : -1;
-        // E0^T = We^T G^T: lane (r, g) holds edge r, features 16 t + 4 g + q
-        const bf16x8 gfr = frag_from_f32(G + (size_t)(ok ? e : e_beg) * EFEAT, ok && g == 0);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const f32x4 a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wef[t], gfr, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-            uint2 pk;
-            pk.x = bf16_bits(fmaxf(a[0] + bev[t][0], 0.f)) | (bf16_bits(fmaxf(a[1] + bev[t][1], 0.f)) << 16);
-            pk.y = bf16_bits(fmaxf(a[2] + bev[t][2], 0.f)) | (bf16_bits(fmaxf(a[3] + bev[t][3], 0.f)) << 16);
-            *(uint2*)&Es[wv][r][16 * t + 4 * g] = pk;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // R^T = Wc^T E0^T, two K steps of 32
-        f32x4 racc[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) racc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const bf16x8 efr = frag_from_bf16(&Es[wv][r][32 * k + 8 * g]);
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-                racc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wcf[k][t], efr, racc[t], 0, 0, 0);
-        }
-        // messages of edge r, features 16 t + 4 g .. + 3
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int f0 = 16 * t + 4 * g;
-            const float4 pv = *(const float4*)(Pm + (size_t)src * HID + f0);
-            const float4 qv = dst >= 0 ? *(const float4*)(Qm + (size_t)dst * HID + f0) : *(const float4*)(qw + f0);
-            float4 mv;
-            mv.x = fmaxf((pv.x + qv.x) + (racc[t][0] + 0.f), 0.f);
-            mv.y = fmaxf((pv.y + qv.y) + (racc[t][1] + 0.f), 0.f);
-            mv.z = fmaxf((pv.z + qv.z) + (racc[t][2] + 0.f), 0.f);
-            mv.w = fmaxf((pv.w + qv.w) + (racc[t][3] + 0.f), 0.f);
-            *(float4*)&Ms[wv][r][f0] = mv;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        // per-node sums in CSR order (every node of the range, edgeless ones
-        // too); the tile's rows are read first, then summed in order
-        const int nrow = min(16, e_end - eb);
-        float mrow[16];
-#pragma unroll
-        for (int row = 0; row < 16; ++row) mrow[row] = Ms[wv][row][lane];
-#pragma unroll
-        for (int row = 0; row < 16; ++row) {
-            if (row >= nrow) break;
-            const int ee = eb + row;
-            while (ee >= cend) {
-                X[(size_t)cur * 2 * HID + HID + lane] = sum;
-                sum = 0.f;
-                ++cur;
-                cend = eoff[cur + 1];
-            }
-            sum += mrow[row];
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-    for (; cur < n1; ++cur) {
-        X[(size_t)cur * 2 * HID + HID + lane] = sum;
+    float pcur = Pm[(size_t)n0 * HID + lane];
+    float pnext = Pm[(size_t)(n0 + (NPW > 1 ? 1 : 0)) * HID + lane];
+    auto flush = [&]() __attribute__((always_inline)) {
+        As[wv * NPW + cur][lane] = (uint16_t)bf16_pair(sum, 0.f);
         sum = 0.f;
+        ++cur;
+        pcur = pnext;
+        pnext = Pm[(size_t)(n0 + min(cur + 1, NPW - 1)) * HID + lane];
+    };
+    for (int eb = 0; eb < ne; eb += 64) {
+        const int e = eb + lane;
+        int dst = N + 1;
+        int p = 0;
+        unsigned long long starts;  // edges that are the first of a node after `cur`
+        uint4 gq = make_uint4(0u, 0u, 0u, 0u);
+        {
+            int first = 0;
+#pragma unroll
+            for (int q = 1; q < NPW; ++q) {
+                const int o = __builtin_amdgcn_readlane(off, q);
+                if (e >= o) {
+                    p = q;
+                    first = o;
+                }
+            }
+            const int i = n0 + p, ni = __shfl(nin, p);
+            starts = __ballot(e == first && e < ne);
+            if (e < ne) {
+                const R2<real> oi = geo[i];
+                const R4<real> si = st[i];
+                const float devi = (float)si.z, vix = (float)si.x, viy = (float)si.y;
+                const int k = e - first;
+                const bool wall = k >= ni;
+                const unsigned kk = (unsigned)(wall ? k - ni : k);
+                const unsigned mx = (unsigned)(wall ? maxw : maxn), ui = (unsigned)i;
+                const unsigned T1 = (1u << lt) - 1u;
+                const size_t at = ((size_t)(ui >> (6 - lt)) * (mx >> lt) + (kk >> lt)) * 64 +
+                                  (((ui & (63u >> lt)) << lt) | (kk & T1));
+                const uint32_t ent = (wall ? wnb : nbr)[at];
+                const int j = (int)(ent & NBR_MASK);
+                const uint32_t code = ent >> NBR_SHIFT;
+                const R2<real> oj = (wall ? wgeo : geo)[j];
+                const float dx = (float)((oi.x - oj.x) - (real)((int)(code & 3u) - 1) * L0);
+                const float dy = (float)((oi.y - oj.y) - (real)((int)((code >> 2) & 3u) - 1) * L1);
+                float f[EFEAT];
+                if (wall) {
+                    edge_features(fs, dx, dy, -vix, -viy, 1.f, (fs.rho0 + devi) * (fs.gx * -dx + fs.gy * -dy), f);
+                    dst = N;
+                } else {
+                    const R4<real> sj = st[j];
+                    edge_features(fs, dx, dy, (float)sj.x - vix, (float)sj.y - viy, 0.f, fs.c2 * ((float)sj.z - devi), f);
+                    dst = j;
+                }
+                gq = make_uint4(bf16_pair(f[0], f[1]), bf16_pair(f[2], f[3]), bf16_pair(f[4], f[5]),
+                                bf16_pair(f[6], f[7]));
+            }
+        }
+        dst *= HID * (int)sizeof(float);
+        *(uint4*)&Gs[wv][lane][0] = gq;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int nt = min(4, (ne - eb + 15) >> 4);
+        for (int t4 = 0; t4 < nt; ++t4) {
+            // Q rows of the tile's edges
+            float qv[16];
+#pragma unroll
+            for (int row = 0; row < 16; ++row)
+                qv[row] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                    qrow, lane * (int)sizeof(float), __builtin_amdgcn_readlane(dst, 16 * t4 + row), 0));
+            // E0^T = We^T G^T: lane (r, g) holds edge r, features 16 t + 4 g + q
+            Frag gf;
+            gf.q = make_uint4(0u, 0u, 0u, 0u);
+            if (g == 0) gf.q = *(const uint4*)&Gs[wv][16 * t4 + r][0];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const f32x4 a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wef[t], gf.v, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                uint2 pk;
+                pk.x = bf16_pair(fmaxf(a[0] + bev[t][0], 0.f), fmaxf(a[1] + bev[t][1], 0.f));
+                pk.y = bf16_pair(fmaxf(a[2] + bev[t][2], 0.f), fmaxf(a[3] + bev[t][3], 0.f));
+                *(uint2*)&Es[wv][r][16 * t + 4 * g] = pk;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            // R^T = Wc^T E0^T, two K steps of 32
+            const bf16x8 e0 = frag_from_bf16(&Es[wv][r][8 * g]), e1 = frag_from_bf16(&Es[wv][r][32 + 8 * g]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                f32x4 a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wcf[0][t], e0, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wcf[1][t], e1, a, 0, 0, 0);
+                *(float4*)&Ms[wv][r][16 * t + 4 * g] = make_float4(a[0], a[1], a[2], a[3]);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            // messages and per-node sums in list order (edgeless nodes too)
+            float mrow[16];
+#pragma unroll
+            for (int row = 0; row < 16; ++row) mrow[row] = Ms[wv][row][lane];
+            const unsigned heads = (unsigned)(starts >> (16 * t4)) & 0xffffu;
+#pragma unroll
+            for (int row = 0; row < 16; ++row) {
+                if (heads & (1u << row)) {
+                    const int to = __builtin_amdgcn_readlane(p, 16 * t4 + row);
+                    while (cur < to) flush();
+                }
+                sum += fmaxf((pcur + qv[row]) + mrow[row], 0.f);
+            }
+        }
     }
+    while (cur < NPW) flush();
+    __syncthreads();
+    // node update, column tile wv
+    const int col = 16 * wv + r;
+    f32x4 acc[RT];
+    float hold[RT][4];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const uint16_t* w = W.WuT + (size_t)col * 2 * HID + 8 * g;
+        const float* h = H + (size_t)(nb0 + 16 * t + r) * HID + 8 * g;
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_from_f32(h, true), frag_from_bf16(w), acc[t], 0, 0, 0);
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_from_f32(h + 32, true), frag_from_bf16(w + 32), acc[t], 0, 0, 0);
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_from_bf16(&As[16 * t + r][8 * g]), frag_from_bf16(w + 64), acc[t], 0, 0, 0);
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_from_bf16(&As[16 * t + r][32 + 8 * g]), frag_from_bf16(w + 96), acc[t], 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) hold[t][q] = H[(size_t)(nb0 + 16 * t + 4 * g + q) * HID + col];
+    }
+    __syncthreads();  // every wavefront has read the block's rows of H before they change
+    const float bu = W.bu[col];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int row = 16 * t + 4 * g + q;
+            const float h = hold[t][q] + fmaxf(acc[t][q] + bu, 0.f);
+            if (W.WaT) H[(size_t)(nb0 + row) * HID + col] = h;  // (the decoder is the last reader)
+            Hb[row][col] = (uint16_t)bf16_pair(h, 0.f);
+        }
+    __syncthreads();
+    if (W.WaT) {
+        const uint16_t *wa = W.WaT + (size_t)col * HID + 8 * g, *wb = W.WbT + (size_t)col * HID + 8 * g;
+        const bf16x8 a0 = frag_from_bf16(wa), a1 = frag_from_bf16(wa + 32), b0 = frag_from_bf16(wb),
+                     b1 = frag_from_bf16(wb + 32);
+        const float bm = W.bm[col];
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            const bf16x8 h0 = frag_from_bf16(&Hb[16 * t + r][8 * g]), h1 = frag_from_bf16(&Hb[16 * t + r][32 + 8 * g]);
+            f32x4 p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h0, a0, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            f32x4 q = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h0, b0, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            p = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h1, a1, p, 0, 0, 0);
+            q = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h1, b1, q, 0, 0, 0);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const size_t o = (size_t)(nb0 + 16 * t + 4 * g + k) * HID + col;
+                Pm[o] = p[k] + bm;
+                Qn[o] = q[k] + 0.f;
+            }
+        }
+        return;
+    }
+    // decoder: D1 = relu(H Wo1 + bo1) through LDS, then the FP32 product with
+    // Wo2, one thread per node and output (the same sums in the same order)
+    float* D1 = &Ms[0][0][0];
+    const uint16_t* wo = W.Wo1T + (size_t)col * HID + 8 * g;
+    const float bo = W.bo1[col];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        f32x4 d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_from_bf16(&Hb[16 * t + r][8 * g]), frag_from_bf16(wo),
+                                                          f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_from_bf16(&Hb[16 * t + r][32 + 8 * g]), frag_from_bf16(wo + 32), d, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) D1[(16 * t + 4 * g + q) * (HID + 4) + col] = fmaxf(d[q] + bo, 0.f);
+    }
+    __syncthreads();
+    const int node = threadIdx.x / NOUT, c = threadIdx.x % NOUT;
+    if (node >= NB) return;
+    float y = W.bo2[c];
+    for (int k = 0; k < HID; ++k) y += D1[node * (HID + 4) + k] * W.Wo2[k * NOUT + c];
+    Y[(size_t)(nb0 + node) * NOUT + c] = y;
 }
 
 // Backward of the messages: dM_e = dA_i [pre_e > 0]; dP_i = sum_e dM_e;

@@ -1912,7 +1912,7 @@ struct Engine final : EngineBase {
         int32_t *ecount = nullptr, *eoff = nullptr, *bsumN = nullptr, *edst = nullptr, *erev = nullptr,
                 *esrc = nullptr;
         bool fused = true;  // inference forward with the fused layer kernel (else edge activations in HBM)
-        float *F = nullptr, *X[3] = {}, *Hs = nullptr, *Z[3] = {}, *P = nullptr, *Q = nullptr, *D1 = nullptr,
+        float *F = nullptr, *X[3] = {}, *Hs = nullptr, *Z[3] = {}, *P = nullptr, *Q[2] = {}, *D1 = nullptr,
               *Y = nullptr, *T = nullptr, *dY = nullptr;
         float *dH = nullptr, *dZ = nullptr, *dA = nullptr, *dPb = nullptr, *dQb = nullptr, *wsum = nullptr;
         float *G = nullptr, *E0 = nullptr, *R = nullptr, *pre[3] = {}, *dM = nullptr, *dE0 = nullptr;
@@ -1964,7 +1964,7 @@ struct Engine final : EngineBase {
         }
         RETCHK(dalloc(A, gn.Hs, n64));
         RETCHK(dalloc(A, gn.P, n64));
-        RETCHK(dalloc(A, gn.Q, n64));
+        for (float*& q : gn.Q) RETCHK(dalloc(A, q, n64 + 2 * gnn::HID));  // + the wall and no-edge rows
         RETCHK(dalloc(A, gn.D1, n64));
         RETCHK(dalloc(A, gn.Y, (size_t)N * gnn::NOUT));
         RETCHK(dalloc(A, gn.T, (size_t)N * gnn::NOUT));
@@ -2130,20 +2130,36 @@ struct Engine final : EngineBase {
             gnn::k_copy64<<<(int)((n + 255) / 256), 256, 0, s>>>((int)M, src, lds, out, ldo);
     }
 
-    static constexpr int FUSED_NPW = 8;  // nodes per wavefront of the fused layer
-
-    void fused_layer(int l)
+    // One layer of the inference forward, Q in gn.Q[l & 1]. 32 nodes per block
+    // once that fills the GPU several times over (half the weight loads per
+    // node), else 16, which shortens each wavefront's chain of edge tiles.
+    void infer_layer(int l)
     {
+        const GnnLayout& L = gn.L;
+        float* p = gn.p;
         const int N = ntot;
-        const int per_block = 4 * FUSED_NPW;
-        gnn::k_gnn_layer_fused<FUSED_NPW><<<(N + per_block - 1) / per_block, 256, 0, s>>>(
-            N, gn.eoff, gn.edst, gn.esrc, gn.G, gn.wt + gn.L.pWe, gn.p + gn.L.be, gn.wt + gn.L.pWc[l], gn.P, gn.Q,
-            gn.p + gn.L.qw[l], gn.X[l]);
+        const bool last = l == 2;
+        const int n = last ? l : l + 1;
+        const gnn::LayerW W = {gn.wt + L.pWe, gn.wt + L.pWc[l], gn.wt + L.pWu[l], last ? nullptr : gn.wt + L.pWa[n],
+                               gn.wt + L.pWb[n], gn.wt + L.pWo1, p + L.be, p + L.bu[l], p + L.bm[n], p + L.qw[n],
+                               p + L.bo1, p + L.Wo2, p + L.bo2};
+        const int lt = ln == 2 ? 1 : ln == 4 ? 2 : 3;
+        if constexpr (D == 2) {
+            auto go = [&](auto npw) {
+                constexpr int NPW = decltype(npw)::value;
+                gnn::k_gnn_layer<real, NPW><<<N / (4 * NPW), 256, 0, s>>>(
+                    dP, tcase, N, lt, nbr, ncnt, wnb, wcnt, geo[cur], wgeo, st[cur], W, gn.Hs, gn.P, gn.Q[l & 1],
+                    gn.Q[1 - (l & 1)], gn.Y);
+            };
+            if (N >= GNN_WIDE) go(std::integral_constant<int, 8>{});
+            else go(std::integral_constant<int, 4>{});
+        }
     }
+    static constexpr int GNN_WIDE = 1 << 16;
 
     int gnn_forward_impl(bool train)
     {
-        // inference: the fused layers (E0, R and the messages stay on chip)
+        // inference: one kernel per layer, nothing per edge in HBM
         if (!train && gn.fused) return gnn_forward_fused();
         RETCHK(gnn_graph(train));
         const GnnLayout& L = gn.L;
@@ -2156,9 +2172,9 @@ struct Engine final : EngineBase {
         gemm<32, gnn::EPI_RELU>(E, gn.G, 32, gn.wt + L.pWe, p + L.be, gn.E0, H);
         for (int l = 0; l < 3; ++l) {
             gemm<64, gnn::EPI_STORE>(N, gn.X[l], 2 * H, gn.wt + L.pWa[l], p + L.bm[l], gn.P, H);
-            gemm<64, gnn::EPI_STORE>(N, gn.X[l], 2 * H, gn.wt + L.pWb[l], nullptr, gn.Q, H);
+            gemm<64, gnn::EPI_STORE>(N, gn.X[l], 2 * H, gn.wt + L.pWb[l], nullptr, gn.Q[0], H);
             gemm<64, gnn::EPI_STORE>(E, gn.E0, H, gn.wt + L.pWc[l], nullptr, gn.R, H);
-            gnn::k_gnn_msg<<<(N + 3) / 4, 256, 0, s>>>(N, gn.eoff, gn.edst, gn.P, gn.Q, gn.R, p + L.qw[l],
+            gnn::k_gnn_msg<<<(N + 3) / 4, 256, 0, s>>>(N, gn.eoff, gn.edst, gn.P, gn.Q[0], gn.R, p + L.qw[l],
                                                        train ? gn.pre[l] : nullptr, gn.X[l]);
             gemm<128, gnn::EPI_RESID>(N, gn.X[l], 2 * H, gn.wt + L.pWu[l], p + L.bu[l], gn.Hs, H, gn.Z[l], H);
             if (l < 2) elem64(N, gn.Hs, H, nullptr, 0, gn.X[l + 1], 2 * H);
@@ -2172,22 +2188,17 @@ struct Engine final : EngineBase {
 
     int gnn_forward_fused()
     {
-        RETCHK(gnn_graph(false, true));
+        // rows of Q are addressed with 32-bit byte offsets
+        if (ntot > (1 << 24) - 2) return ctx->fail(SPHX_ENOMEM, "too many particles for the surrogate");
+        RETCHK(gnn_nodes(false));
         const GnnLayout& L = gn.L;
-        const int N = ntot;
         float* p = gn.p;
-        constexpr int H = gnn::HID;
-        gemm<32, gnn::EPI_RELU>(N, gn.F, 32, gn.wt + L.pWn, p + L.bn, gn.X[0], 2 * H);
-        elem64(N, gn.X[0], 2 * H, nullptr, 0, gn.Hs, H);
-        for (int l = 0; l < 3; ++l) {
-            gemm<64, gnn::EPI_STORE>(N, gn.X[l], 2 * H, gn.wt + L.pWa[l], p + L.bm[l], gn.P, H);
-            gemm<64, gnn::EPI_STORE>(N, gn.X[l], 2 * H, gn.wt + L.pWb[l], nullptr, gn.Q, H);
-            fused_layer(l);
-            gemm<128, gnn::EPI_RESID>(N, gn.X[l], 2 * H, gn.wt + L.pWu[l], p + L.bu[l], gn.Hs, H, gn.Z[l], H);
-            if (l < 2) elem64(N, gn.Hs, H, nullptr, 0, gn.X[l + 1], 2 * H);
-        }
-        gemm<64, gnn::EPI_RELU>(N, gn.Hs, H, gn.wt + L.pWo1, p + L.bo1, gn.D1, H);
-        gnn::k_gnn_out<<<nblk(N), BLOCK, 0, s>>>(N, gn.D1, p + L.Wo2, p + L.bo2, gn.Y);
+        const int N = ntot;
+        if constexpr (D == 2)
+            gnn::k_gnn_encode<real><<<N / 64, 256, 0, s>>>(dP, tcase, N, ncnt, wcnt, st[cur], gn.wt + L.pWn, p + L.bn,
+                                                           gn.wt + L.pWa[0], p + L.bm[0], gn.wt + L.pWb[0], p + L.qw[0],
+                                                           gn.Hs, gn.P, gn.Q[0]);
+        for (int l = 0; l < 3; ++l) infer_layer(l);
         HIPCHK(hipGetLastError());
         gn.gen = conf_gen;
         return SPHX_OK;
@@ -2352,12 +2363,12 @@ struct Engine final : EngineBase {
         const long long E = gn.E;
         RETCHK(time_launches(reps, &ms[5], [&] { gemm<64, gnn::EPI_STORE>(E, gn.E0, H, gn.wt + L.pWc[0], nullptr, gn.R, H); }));
         RETCHK(time_launches(reps, &ms[6], [&] {
-            gnn::k_gnn_msg<<<(N + 3) / 4, 256, 0, s>>>(N, gn.eoff, gn.edst, gn.P, gn.Q, gn.R, p + L.qw[0], nullptr,
+            gnn::k_gnn_msg<<<(N + 3) / 4, 256, 0, s>>>(N, gn.eoff, gn.edst, gn.P, gn.Q[0], gn.R, p + L.qw[0], nullptr,
                                                        gn.X[0]);
         }));
         // the fused forward (the default)
         RETCHK(whole(true, &ms[3]));
-        RETCHK(time_launches(reps, &ms[0], [&] { fused_layer(0); }));
+        RETCHK(time_launches(reps, &ms[0], [&] { infer_layer(0); }));
         RETCHK(time_launches(reps, &ms[1], [&] {
             if constexpr (D == 2) {
                 by_lanes([&](auto t) {
