@@ -29,6 +29,7 @@ constexpr int HID = 64;
 constexpr int FPAD = 32;   // padded encoder input width
 constexpr int EFEAT = 8;   // edge features used
 constexpr int NOUT = 3;
+constexpr unsigned ROW_BYTES = HID * sizeof(float);  // of an FP32 row; row offsets are 32-bit
 constexpr int WALL_EDGE = -1;  // edst < 0: wall edge, wall index -1 - edst
 
 typedef __bf16 bf16;
@@ -150,18 +151,60 @@ __global__ __launch_bounds__(256) void k_gemm64(int M, const float* __restrict__
 
 // ---------------------------------------------------------------------
 // Weight gradient dW[KIN x 64] = X^T dZ over M rows, split over blocks of
-// `rows` rows each (partials summed later in a fixed order), and the column
-// sums of dZ (bias gradient) in FP32. Each 32-row step stages X and dZ,
-// rounded to bf16 and transposed, in LDS; wavefront w computes output column
-// tile w for all KIN/16 row tiles.
+// `rows` rows each (partials summed later in a fixed order), and with `bpart`
+// the column sums of dZ (bias gradient) in FP32, row by row. Each step takes
+// WROWS rows: a wavefront loads 16 of them with one lane per column, so that
+// a lane holds 16 rows of its column, which it rounds to bf16 and writes as
+// whole 16-byte pieces of the transposed LDS arrays; the next step's loads
+// are in flight while wavefront w computes output column tile w for all
+// KIN/16 row tiles. Bound by HBM: X and dZ are read once. (A load, a
+// conversion and a 2-byte LDS write per element, and the bias from a second
+// serial read of dZ: 100 us for 205k rows of 64 + 64 columns, 21 us of
+// traffic.)
+constexpr int WROWS = 64;      // rows per step
+constexpr int WPAD = WROWS + 8;
+
+// Round the 16 rows of a lane's column and store them from row `at`.
+__device__ __forceinline__ void store_rows16(uint16_t* p, const float v[16])
+{
+    uint4 a, b;
+    a.x = bf16_pair(v[0], v[1]);
+    a.y = bf16_pair(v[2], v[3]);
+    a.z = bf16_pair(v[4], v[5]);
+    a.w = bf16_pair(v[6], v[7]);
+    b.x = bf16_pair(v[8], v[9]);
+    b.y = bf16_pair(v[10], v[11]);
+    b.z = bf16_pair(v[12], v[13]);
+    b.w = bf16_pair(v[14], v[15]);
+    *(uint4*)p = a;
+    *(uint4*)(p + 8) = b;
+}
+
+// acc[t] += X^T dZ of one staged step: rows of Xs are X's columns (TM tiles
+// of 16), Zs's are dZ's, both bf16 with WROWS rows contiguous.
+template <int TM>
+__device__ __forceinline__ void wgrad_step(const uint16_t (*Xs)[WPAD], const uint16_t (*Zs)[WPAD], int w, int r, int g,
+                                           f32x4 acc[TM])
+{
+#pragma unroll
+    for (int k = 0; k < WROWS; k += 32) {
+        const bf16x8 fb = frag_from_bf16(&Zs[16 * w + r][k + 8 * g]);
+#pragma unroll
+        for (int t = 0; t < TM; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_from_bf16(&Xs[16 * t + r][k + 8 * g]), fb, acc[t], 0, 0, 0);
+    }
+}
+
 template <int KIN>
 __global__ __launch_bounds__(256) void k_wgrad(int M, int rows, const float* __restrict__ X, int ldx,
                                                const float* __restrict__ dZ, int ldz, float* __restrict__ part,
                                                float* __restrict__ bpart)
 {
     constexpr int TM = KIN / 16;
-    __shared__ __align__(16) uint16_t Xs[KIN][32 + 8];
-    __shared__ __align__(16) uint16_t Zs[HID][32 + 8];
+    constexpr int XL = KIN / 4;  // X values per lane and step (16 rows x KIN columns over 64 lanes)
+    __shared__ __align__(16) uint16_t Xs[KIN][WPAD];
+    __shared__ __align__(16) uint16_t Zs[HID][WPAD];
+    __shared__ float Zf[WROWS][HID];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int r = lane & 15, g = lane >> 4;
     f32x4 acc[TM];
@@ -170,29 +213,41 @@ __global__ __launch_bounds__(256) void k_wgrad(int M, int rows, const float* __r
     float bsum = 0.f;
     const int r0 = blockIdx.x * rows;
     const int r1 = min(r0 + rows, M);
-    for (int rb = r0; rb < r1; rb += 32) {
-        // stage: X chunk 32 x KIN and dZ chunk 32 x 64, transposed
-        for (int idx = threadIdx.x; idx < 32 * KIN; idx += 256) {
-            const int rr = idx / KIN, k = idx % KIN;
-            const int row = rb + rr;
-            Xs[k][rr] = (uint16_t)(row < r1 ? bf16_bits(X[(size_t)row * ldx + k]) : 0u);
-        }
-        for (int idx = threadIdx.x; idx < 32 * HID; idx += 256) {
-            const int rr = idx / HID, n = idx % HID;
-            const int row = rb + rr;
-            const float z = row < r1 ? dZ[(size_t)row * ldz + n] : 0.f;
-            Zs[n][rr] = (uint16_t)bf16_bits(z);
-        }
-        if (threadIdx.x < HID)
-            for (int rr = 0; rr < 32 && rb + rr < r1; ++rr) bsum += dZ[(size_t)(rb + rr) * ldz + threadIdx.x];
-        __syncthreads();
-        Frag fb;
-        fb.q = *(const uint4*)&Zs[16 * w + r][8 * g];
+    float z[16], x[XL];
+    auto load = [&](int rb) __attribute__((always_inline)) {
 #pragma unroll
-        for (int t = 0; t < TM; ++t) {
-            Frag fa;
-            fa.q = *(const uint4*)&Xs[16 * t + r][8 * g];
-            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa.v, fb.v, acc[t], 0, 0, 0);
+        for (int q = 0; q < 16; ++q) {
+            const int row = rb + 16 * w + q;
+            z[q] = row < r1 ? dZ[(size_t)row * ldz + lane] : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < XL; ++q) {
+            // KIN = 32: half a wavefront per row, rows q and q + 8
+            const int row = rb + 16 * w + (KIN == 32 ? 8 * (lane >> 5) + q : q % 16);
+            const int col = KIN == 32 ? (lane & 31) : lane + 64 * (q / 16);
+            x[q] = row < r1 ? X[(size_t)row * ldx + col] : 0.f;
+        }
+    };
+    load(r0);
+    for (int rb = r0; rb < r1; rb += WROWS) {
+        store_rows16(&Zs[lane][16 * w], z);
+        if constexpr (KIN == 32) {
+            *(uint4*)&Xs[lane & 31][16 * w + 8 * (lane >> 5)] = make_uint4(
+                bf16_pair(x[0], x[1]), bf16_pair(x[2], x[3]), bf16_pair(x[4], x[5]), bf16_pair(x[6], x[7]));
+        } else {
+#pragma unroll
+            for (int c = 0; c < KIN / 64; ++c) store_rows16(&Xs[lane + 64 * c][16 * w], x + 16 * c);
+        }
+        if (bpart)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) Zf[16 * w + q][lane] = z[q];
+        __syncthreads();
+        if (rb + WROWS < r1) load(rb + WROWS);
+        wgrad_step<TM>(Xs, Zs, w, r, g, acc);
+        if (bpart && threadIdx.x < HID) {
+            const int n = min(WROWS, r1 - rb);
+#pragma unroll 16
+            for (int q = 0; q < n; ++q) bsum += Zf[q][threadIdx.x];
         }
         __syncthreads();
     }
@@ -201,18 +256,49 @@ __global__ __launch_bounds__(256) void k_wgrad(int M, int rows, const float* __r
     for (int t = 0; t < TM; ++t)
 #pragma unroll
         for (int q = 0; q < 4; ++q) out[(size_t)(16 * t + 4 * g + q) * HID + 16 * w + r] = acc[t][q];
-    if (threadIdx.x < HID) bpart[(size_t)blockIdx.x * HID + threadIdx.x] = bsum;
+    if (bpart && threadIdx.x < HID) bpart[(size_t)blockIdx.x * HID + threadIdx.x] = bsum;
 }
 
-// out[j] (+)= sum over b of part[b][j], b ascending (deterministic).
-__global__ __launch_bounds__(256) void k_reduce_parts(int nb, int len, const float* __restrict__ part,
-                                                      float* __restrict__ out, int accumulate)
+// out[j] = sum over b of part[b][j], b ascending (deterministic), for two
+// arrays in one launch: blocks below nblk1 the first, the rest the second.
+// A block takes 16 columns: 256 rows at a time go through LDS with 16 loads
+// in flight per thread, then one lane per column adds them in order. (One
+// thread per column reading its column row by row waited out a memory round
+// trip per few rows: 185 us for 1024 x 4096, 17 MB.)
+constexpr int RCOLS = 16;
+__global__ __launch_bounds__(256) void k_reduce_parts(int nb, int nblk1, int len, const float* __restrict__ part,
+                                                      float* __restrict__ out, int len2,
+                                                      const float* __restrict__ part2, float* __restrict__ out2)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= len) return;
+    __shared__ float sh[256][RCOLS + 1];
+    int bx = blockIdx.x;
+    if (bx >= nblk1) {
+        bx -= nblk1;
+        len = len2;
+        part = part2;
+        out = out2;
+    }
+    const int c = threadIdx.x % RCOLS, rr = threadIdx.x / RCOLS;
+    const int j = bx * RCOLS + c;
     float s = 0.f;
-    for (int b = 0; b < nb; ++b) s += part[(size_t)b * len + j];
-    out[j] = accumulate ? out[j] + s : s;
+    for (int b0 = 0; b0 < nb; b0 += 256) {
+        float v[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int b = b0 + rr + 16 * q;
+            v[q] = b < nb && j < len ? part[(size_t)b * len + j] : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q) sh[rr + 16 * q][c] = v[q];
+        __syncthreads();
+        if (threadIdx.x < RCOLS) {
+            const int n = min(256, nb - b0);
+#pragma unroll 16
+            for (int b = 0; b < n; ++b) s += sh[b][c];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x < RCOLS && j < len) out[j] = s;
 }
 
 // Column sums of a [M x 64] FP32 matrix in row blocks (partials).
@@ -221,7 +307,15 @@ __global__ __launch_bounds__(64) void k_colsum64(int M, int rows, const float* _
 {
     const int r0 = blockIdx.x * rows, r1 = min(r0 + rows, M);
     float s = 0.f;
-    for (int r = r0; r < r1; ++r) s += A[(size_t)r * lda + threadIdx.x];
+    int r = r0;
+    for (; r + 32 <= r1; r += 32) {  // 32 loads in flight
+        float v[32];
+#pragma unroll
+        for (int q = 0; q < 32; ++q) v[q] = A[(size_t)(r + q) * lda + threadIdx.x];
+#pragma unroll
+        for (int q = 0; q < 32; ++q) s += v[q];
+    }
+    for (; r < r1; ++r) s += A[(size_t)r * lda + threadIdx.x];
     part[(size_t)blockIdx.x * HID + threadIdx.x] = s;
 }
 
@@ -245,126 +339,6 @@ __device__ __forceinline__ float wendland_ratio(float q)
 {
     const float s = fmaxf(1.f - 0.5f * q, 0.f);
     return s * s * s * s * (1.f + 2.f * q);
-}
-
-// One thread per slot. Edge features (x_j - x_i)/h, r/h, (v_j - v_i)/u_ref,
-// W(r)/W(0), wall flag, pressure difference (p_j - p_i)/(rho0 |g| h) (for a
-// wall the one-sided wall state, p_w - p_i = rho_i g.(x_w - x_i)), taken in
-// FP32 from the density deviations before any rounding; node features
-// v/u_ref, (rho - rho0)/(0.01 rho0), inner and contact counts / 32 and / 16
-// (2D).
-//
-// G rows hold `ldg` floats: FPAD (zero-padded, for the training path's
-// encoder product) or EFEAT (the features alone, for the fused inference
-// layer). esrc (may be null) receives each edge's particle; the reverse
-// edges (erev, training only: the backward of Q_j) are searched only when
-// erev is given.
-template <typename real, int T>
-__global__ __launch_bounds__(BLOCK) void k_gnn_edges(
-    const KP<real>* __restrict__ Pt, const int32_t* __restrict__ tcase, int ntiles, const int32_t* __restrict__ eoff,
-    const uint32_t* __restrict__ nbr, const int32_t* __restrict__ ncnt, const uint32_t* __restrict__ wnb,
-    const int32_t* __restrict__ wcnt, const R2<real>* __restrict__ geo, const R2<real>* __restrict__ wgeo,
-    const R4<real>* __restrict__ st, int32_t* __restrict__ edst, int32_t* __restrict__ erev,
-    int32_t* __restrict__ esrc, float* __restrict__ G, int ldg, float* __restrict__ F)
-{
-    const int tile = wave_tile();
-    if (tile >= ntiles) return;
-    const KP<real>& P = Pt[tcase[tile]];
-    const int i = tile * TILE + (threadIdx.x & 63);
-    float* f = F + (size_t)i * FPAD;
-    if (i >= P.fbase + P.nf) {
-        for (int k = 0; k < FPAD; ++k) f[k] = 0.f;
-        return;
-    }
-    const float inv_u = (float)(1.0 / P.u_ref);
-    const float inv_h = (float)P.inv_h;
-    const float gx = (float)P.g[0], gy = (float)P.g[1];
-    const float gmag = sqrtf(gx * gx + gy * gy + (float)P.g[2] * (float)P.g[2]);
-    const float inv_pscale = 1.f / ((float)P.rho0 * gmag) * inv_h;
-    const float c2 = (float)P.c2;
-    const R4<real> si = st[i];
-    const float devi = (float)si.z;
-    const float vix = (float)si.x, viy = (float)si.y;
-    const int nin = ncnt[i], nwl = wcnt[i];
-    f[0] = vix * inv_u;
-    f[1] = viy * inv_u;
-    f[2] = (float)si.z / (0.01f * (float)P.rho0);
-    f[3] = (float)nin / 32.f;
-    f[4] = (float)nwl / 16.f;
-    for (int k = 5; k < FPAD; ++k) f[k] = 0.f;
-    const R2<real> oi = geo[i];
-    int e = eoff[i];
-    auto edge = [&](int e_, float dx, float dy, float dvx, float dvy, float wall, float dpres) {
-        float* gr = G + (size_t)e_ * ldg;
-        if (esrc) esrc[e_] = i;
-        const float rr = sqrtf(dx * dx + dy * dy);
-        gr[0] = -dx * inv_h;  // x_j - x_i
-        gr[1] = -dy * inv_h;
-        gr[2] = rr * inv_h;
-        gr[3] = dvx * inv_u;
-        gr[4] = dvy * inv_u;
-        gr[5] = wendland_ratio(rr * inv_h);
-        gr[6] = wall;
-        gr[7] = dpres * inv_pscale;
-        for (int k = EFEAT; k < ldg; ++k) gr[k] = 0.f;
-    };
-    for (int k = 0; k < nin; ++k, ++e) {
-        const uint32_t ent = nbr[ell_at<T>(i, k, P.maxn)];
-        const int j = (int)(ent & NBR_MASK);
-        const uint32_t code = ent >> NBR_SHIFT;
-        const R2<real> oj = geo[j];
-        const float dx = (float)((oi.x - oj.x) - (real)((int)(code & 3u) - 1) * P.L[0]);
-        const float dy = (float)((oi.y - oj.y) - (real)((int)((code >> 2) & 3u) - 1) * P.L[1]);
-        const R4<real> sj = st[j];
-        edge(e, dx, dy, (float)sj.x - vix, (float)sj.y - viy, 0.f, c2 * ((float)sj.z - devi));
-        edst[e] = j;
-        if (erev) {
-            // the reverse edge: i in the inner list of j (the lists are symmetric)
-            int rv = -1;
-            const int nj = ncnt[j];
-            for (int kk = 0; kk < nj; ++kk)
-                if ((int)(nbr[ell_at<T>(j, kk, P.maxn)] & NBR_MASK) == i) {
-                    rv = eoff[j] + kk;
-                    break;
-                }
-            erev[e] = rv;
-        }
-    }
-    for (int k = 0; k < nwl; ++k, ++e) {
-        const uint32_t ent = wnb[ell_at<T>(i, k, P.maxw)];
-        const int wj = (int)(ent & NBR_MASK);
-        const uint32_t code = ent >> NBR_SHIFT;
-        const R2<real> ow = wgeo[wj];
-        const float dx = (float)((oi.x - ow.x) - (real)((int)(code & 3u) - 1) * P.L[0]);
-        const float dy = (float)((oi.y - ow.y) - (real)((int)((code >> 2) & 3u) - 1) * P.L[1]);
-        edge(e, dx, dy, -vix, -viy, 1.f, ((float)P.rho0 + devi) * (gx * -dx + gy * -dy));
-        edst[e] = -1 - wj;
-        if (erev) erev[e] = -1;
-    }
-}
-
-// ---------------------------------------------------------------------
-// Messages: one wavefront per node row, lane = feature.
-//   pre_e = P_i + (Q_j | qw) + R_e,  A_i = sum_e relu(pre_e) -> X[i][64 + f]
-__global__ __launch_bounds__(256) void k_gnn_msg(int N, const int32_t* __restrict__ eoff,
-                                                 const int32_t* __restrict__ edst, const float* __restrict__ P,
-                                                 const float* __restrict__ Q, const float* __restrict__ R,
-                                                 const float* __restrict__ qw, float* __restrict__ pre_out,
-                                                 float* __restrict__ X)
-{
-    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i >= N) return;
-    const int f = threadIdx.x & 63;
-    const float p = P[(size_t)i * HID + f];
-    const float q0 = qw[f];
-    float acc = 0.f;
-    for (int e = eoff[i]; e < eoff[i + 1]; ++e) {
-        const int d = edst[e];
-        const float pre = p + (d >= 0 ? Q[(size_t)d * HID + f] : q0) + R[(size_t)e * HID + f];
-        if (pre_out) pre_out[(size_t)e * HID + f] = pre;
-        acc += fmaxf(pre, 0.f);
-    }
-    X[(size_t)i * 2 * HID + HID + f] = acc;
 }
 
 // Constants of a case's features.
@@ -401,12 +375,124 @@ __device__ __forceinline__ void edge_features(const FeatScale& c, float dx, floa
     f[7] = dpres * c.inv_pscale;
 }
 
-// Inference runs the network in four launches, straight from the neighbour
-// lists: the node encoder (with layer 0's P and Q) and one kernel per layer
-// (with the next layer's P and Q, or the decoder). Nothing per edge reaches
-// HBM, and no edge count is needed on the host. Every value is rounded where
-// and summed in the order in which the separate products and sums of the
-// training path round and sum it, so the predictions agree bit for bit.
+// The edges in CSR order with their features: EL lanes per slot, each taking
+// every EL-th entry. Edge features (x_j - x_i)/h, r/h, (v_j - v_i)/u_ref,
+// W(r)/W(0), wall flag, pressure difference (p_j - p_i)/(rho0 |g| h) (for a
+// wall the one-sided wall state, p_w - p_i = rho_i g.(x_w - x_i)), taken in
+// FP32 from the density deviations before any rounding; node features
+// v/u_ref, (rho - rho0)/(0.01 rho0), inner and contact counts / 32 and / 16
+// (2D).
+//
+// G rows hold `ldg` floats: EFEAT (the features alone) or FPAD (zero-padded,
+// for the unfused encoder product). esrc receives each edge's particle as the
+// byte offset of its row of 64 floats; the reverse edges (erev, for the
+// backward of Q_j) are searched only when erev is given. (One thread per slot
+// left 3 200 wavefronts with a serial search each: 700 us at 205k nodes.)
+constexpr int EL = 8;
+template <typename real, int T>
+__global__ __launch_bounds__(BLOCK) void k_gnn_edges(
+    const KP<real>* __restrict__ Pt, const int32_t* __restrict__ tcase, int N, const int32_t* __restrict__ eoff,
+    const uint32_t* __restrict__ nbr, const int32_t* __restrict__ ncnt, const uint32_t* __restrict__ wnb,
+    const int32_t* __restrict__ wcnt, const R2<real>* __restrict__ geo, const R2<real>* __restrict__ wgeo,
+    const R4<real>* __restrict__ st, int32_t* __restrict__ edst, int32_t* __restrict__ erev,
+    int32_t* __restrict__ esrc, float* __restrict__ G, int ldg, float* __restrict__ F)
+{
+    const int i = (blockIdx.x * BLOCK + threadIdx.x) / EL, l = threadIdx.x % EL;
+    if (i >= N) return;
+    const KP<real>& P = Pt[tcase[i / TILE]];
+    float4* f = (float4*)(F + (size_t)i * FPAD);
+    const bool used = i < P.fbase + P.nf;
+    const R4<real> si = used ? st[i] : R4<real>{};
+    const float devi = (float)si.z;
+    const float vix = (float)si.x, viy = (float)si.y;
+    const int nin = used ? ncnt[i] : 0, nwl = used ? wcnt[i] : 0;
+    const FeatScale c = feat_scale(P);
+    // node features: FPAD floats, four per lane
+    static_assert(FPAD == 4 * EL, "one float4 of node features per lane");
+    float4 fv = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (used && l == 0)
+        fv = make_float4(vix * c.inv_u, viy * c.inv_u, (float)si.z / (0.01f * (float)P.rho0), (float)nin / 32.f);
+    if (used && l == 1) fv.x = (float)nwl / 16.f;
+    f[l] = fv;
+    if (!used) return;
+    const R2<real> oi = geo[i];
+    const int e0 = eoff[i];
+    auto edge = [&](int e, float dx, float dy, float dvx, float dvy, float wall, float dpres) {
+        float q[EFEAT];
+        edge_features(c, dx, dy, dvx, dvy, wall, dpres, q);
+        float4* gr = (float4*)(G + (size_t)e * ldg);
+        gr[0] = make_float4(q[0], q[1], q[2], q[3]);
+        gr[1] = make_float4(q[4], q[5], q[6], q[7]);
+        for (int k = EFEAT / 4; k < ldg / 4; ++k) gr[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+        esrc[e] = (int)((unsigned)i * ROW_BYTES);
+    };
+    for (int k = l; k < nin; k += EL) {
+        const int e = e0 + k;
+        const uint32_t ent = nbr[ell_at<T>(i, k, P.maxn)];
+        const int j = (int)(ent & NBR_MASK);
+        const uint32_t code = ent >> NBR_SHIFT;
+        const R2<real> oj = geo[j];
+        const float dx = (float)((oi.x - oj.x) - (real)((int)(code & 3u) - 1) * P.L[0]);
+        const float dy = (float)((oi.y - oj.y) - (real)((int)((code >> 2) & 3u) - 1) * P.L[1]);
+        const R4<real> sj = st[j];
+        edge(e, dx, dy, (float)sj.x - vix, (float)sj.y - viy, 0.f, c.c2 * ((float)sj.z - devi));
+        edst[e] = j;
+        if (erev) {
+            // the reverse edge: i in the inner list of j (the lists are symmetric)
+            int rv = -1;
+            const int nj = ncnt[j];
+            for (int kk = 0; kk < nj; ++kk)
+                if ((int)(nbr[ell_at<T>(j, kk, P.maxn)] & NBR_MASK) == i) {
+                    rv = eoff[j] + kk;
+                    break;
+                }
+            erev[e] = rv;
+        }
+    }
+    for (int k = l; k < nwl; k += EL) {
+        const int e = e0 + nin + k;
+        const uint32_t ent = wnb[ell_at<T>(i, k, P.maxw)];
+        const int wj = (int)(ent & NBR_MASK);
+        const uint32_t code = ent >> NBR_SHIFT;
+        const R2<real> ow = wgeo[wj];
+        const float dx = (float)((oi.x - ow.x) - (real)((int)(code & 3u) - 1) * P.L[0]);
+        const float dy = (float)((oi.y - ow.y) - (real)((int)((code >> 2) & 3u) - 1) * P.L[1]);
+        edge(e, dx, dy, -vix, -viy, 1.f, (c.rho0 + devi) * (c.gx * -dx + c.gy * -dy));
+        edst[e] = -1 - wj;
+        if (erev) erev[e] = -1;
+    }
+}
+
+// ---------------------------------------------------------------------
+// Messages of the unfused layer (sphx_gnn_profile's comparison): one
+// wavefront per node row, lane = feature,
+//   A_i = sum_e relu(P_i + (Q_j | qw) + R_e) -> X[i][64 + f]
+__global__ __launch_bounds__(256) void k_gnn_msg(int N, const int32_t* __restrict__ eoff,
+                                                 const int32_t* __restrict__ edst, const float* __restrict__ P,
+                                                 const float* __restrict__ Q, const float* __restrict__ R,
+                                                 const float* __restrict__ qw, float* __restrict__ X)
+{
+    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= N) return;
+    const int f = threadIdx.x & 63;
+    const float p = P[(size_t)i * HID + f];
+    const float q0 = qw[f];
+    float acc = 0.f;
+    for (int e = eoff[i]; e < eoff[i + 1]; ++e) {
+        const int d = edst[e];
+        const float pre = p + (d >= 0 ? Q[(size_t)d * HID + f] : q0) + R[(size_t)e * HID + f];
+        acc += fmaxf(pre, 0.f);
+    }
+    X[(size_t)i * 2 * HID + HID + f] = acc;
+}
+
+// The forward pass is four launches, straight from the neighbour lists: the
+// node encoder (with layer 0's P and Q) and one kernel per layer (with the
+// next layer's P and Q, or the decoder). Nothing per edge reaches HBM in
+// inference, and no edge count is needed on the host; a training pass keeps
+// one bit per message (its sign, for the backward pass) and the node arrays.
+// Every value is rounded where and summed in the order in which the unfused
+// products and sums round and sum it, so the two agree bit for bit.
 
 // Rows N and N + 1 of a Q array: the learned vector that stands for Q_j at a
 // wall edge, and one so negative that its message is 0 (a tile row without an
@@ -426,8 +512,8 @@ __global__ __launch_bounds__(256) void k_gnn_encode(
     const KP<real>* __restrict__ Pt, const int32_t* __restrict__ tcase, int N, const int32_t* __restrict__ ncnt,
     const int32_t* __restrict__ wcnt, const R4<real>* __restrict__ st, const uint16_t* __restrict__ WnT,
     const float* __restrict__ bn, const uint16_t* __restrict__ WaT, const float* __restrict__ bm,
-    const uint16_t* __restrict__ WbT, const float* __restrict__ qw, float* __restrict__ H, float* __restrict__ Pm,
-    float* __restrict__ Qm)
+    const uint16_t* __restrict__ WbT, const float* __restrict__ qw, float* __restrict__ H, int ldh,
+    float* __restrict__ Pm, float* __restrict__ Qm)
 {
     special_rows(Qm, N, qw);
     __shared__ __align__(16) uint16_t Hs[4][16][HID + 8];
@@ -454,7 +540,7 @@ __global__ __launch_bounds__(256) void k_gnn_encode(
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const float h = fmaxf(a[q] + bv, 0.f);
-            H[(size_t)(m0 + 4 * g + q) * HID + 16 * t + r] = h;
+            H[(size_t)(m0 + 4 * g + q) * ldh + 16 * t + r] = h;
             Hs[wv][4 * g + q][16 * t + r] = (uint16_t)bf16_pair(h, 0.f);
         }
     }
@@ -487,6 +573,15 @@ struct LayerW {
     const float *be, *bu, *bm, *qn, *bo1, *Wo2, *bo2;  // qn: the next layer's wall vector
 };
 
+// What a training pass keeps of a layer: the sign bits of its messages (bit f
+// of mask[e], e in CSR order), A in columns 64.. of X [N x 128] (whose first
+// 64 columns are H), the update's pre-activation Z and the decoder's D1.
+struct LayerKeep {
+    const int32_t* eoff;
+    unsigned long long* mask;
+    float *X, *Z, *D1;
+};
+
 // One message-passing layer over the neighbour lists: for every node i, over
 // its edges e (inner, then contact entries, in list order),
 //   E0_e = relu(G_e We + be),  R_e = E0_e Wc,
@@ -510,13 +605,13 @@ struct LayerW {
 // (173 scalar instructions a tile, 553 us). The node
 // update follows in the same block, on the rows it holds: wavefront w
 // computes output columns 16 w .. 16 w + 15.
-template <typename real, int NPW>
+template <typename real, int NPW, bool TRAIN>
 __global__ __launch_bounds__(256, 4) void k_gnn_layer(
     const KP<real>* __restrict__ Pt, const int32_t* __restrict__ tcase, int N, int lt,
     const uint32_t* __restrict__ nbr, const int32_t* __restrict__ ncnt, const uint32_t* __restrict__ wnb,
     const int32_t* __restrict__ wcnt, const R2<real>* __restrict__ geo, const R2<real>* __restrict__ wgeo,
-    const R4<real>* __restrict__ st, LayerW W, float* H, float* Pm, const float* __restrict__ Qm,
-    float* __restrict__ Qn, float* __restrict__ Y)
+    const R4<real>* __restrict__ st, LayerW W, const float* H, int ldh, float* Ho, int ldo, float* Pm,
+    const float* __restrict__ Qm, float* __restrict__ Qn, float* __restrict__ Y, LayerKeep K)
 {
     constexpr int NB = 4 * NPW;   // nodes per block
     constexpr int RT = NB / 16;   // row tiles of the node update
@@ -534,7 +629,7 @@ __global__ __launch_bounds__(256, 4) void k_gnn_layer(
     const KP<real>& P = Pt[tcase[nb0 / TILE]];
     if (W.WaT) special_rows(Qn, N, W.qn);
     const __amdgpu_buffer_rsrc_t qrow =
-        __builtin_amdgcn_make_buffer_rsrc((void*)Qm, 0, (int)((unsigned)(N + 2) * HID * sizeof(float)), 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc((void*)Qm, 0, (int)((unsigned)(N + 2) * ROW_BYTES), 0x00020000);
     const FeatScale fs = feat_scale(P);
     const int maxn = P.maxn, maxw = P.maxw;
     const real L0 = P.L[0], L1 = P.L[1];
@@ -563,6 +658,7 @@ __global__ __launch_bounds__(256, 4) void k_gnn_layer(
 #pragma unroll
         for (int q = 0; q < 4; ++q) bev[t][q] = W.be[16 * t + 4 * g + q];
     }
+    const int ebase = TRAIN ? K.eoff[n0] : 0;
     // the reduction: lane = feature, running node `cur` (uniform)
     int cur = 0;
     float sum = 0.f;
@@ -570,6 +666,7 @@ __global__ __launch_bounds__(256, 4) void k_gnn_layer(
     float pnext = Pm[(size_t)(n0 + (NPW > 1 ? 1 : 0)) * HID + lane];
     auto flush = [&]() __attribute__((always_inline)) {
         As[wv * NPW + cur][lane] = (uint16_t)bf16_pair(sum, 0.f);
+        if constexpr (TRAIN) K.X[(size_t)(n0 + cur) * 2 * HID + HID + lane] = sum;
         sum = 0.f;
         ++cur;
         pcur = pnext;
@@ -623,7 +720,7 @@ __global__ __launch_bounds__(256, 4) void k_gnn_layer(
                                 bf16_pair(f[6], f[7]));
             }
         }
-        dst *= HID * (int)sizeof(float);
+        dst = (int)((unsigned)dst * ROW_BYTES);
         *(uint4*)&Gs[wv][lane][0] = gq;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -667,14 +764,22 @@ __global__ __launch_bounds__(256, 4) void k_gnn_layer(
 #pragma unroll
             for (int row = 0; row < 16; ++row) mrow[row] = Ms[wv][row][lane];
             const unsigned heads = (unsigned)(starts >> (16 * t4)) & 0xffffu;
+            unsigned long long sign = 0ull;  // lane row < 16: the sign bits of edge `row`
 #pragma unroll
             for (int row = 0; row < 16; ++row) {
                 if (heads & (1u << row)) {
                     const int to = __builtin_amdgcn_readlane(p, 16 * t4 + row);
                     while (cur < to) flush();
                 }
-                sum += fmaxf((pcur + qv[row]) + mrow[row], 0.f);
+                const float pre = (pcur + qv[row]) + mrow[row];
+                if constexpr (TRAIN) {
+                    const unsigned long long m = __ballot(pre > 0.f);
+                    if (lane == row) sign = m;
+                }
+                sum += fmaxf(pre, 0.f);
             }
+            if constexpr (TRAIN)
+                if (lane < 16 && eb + 16 * t4 + lane < ne) K.mask[(size_t)(ebase + eb + 16 * t4 + lane)] = sign;
         }
     }
     while (cur < NPW) flush();
@@ -687,13 +792,13 @@ __global__ __launch_bounds__(256, 4) void k_gnn_layer(
     for (int t = 0; t < RT; ++t) {
         acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
         const uint16_t* w = W.WuT + (size_t)col * 2 * HID + 8 * g;
-        const float* h = H + (size_t)(nb0 + 16 * t + r) * HID + 8 * g;
+        const float* h = H + (size_t)(nb0 + 16 * t + r) * ldh + 8 * g;
         acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_from_f32(h, true), frag_from_bf16(w), acc[t], 0, 0, 0);
         acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_from_f32(h + 32, true), frag_from_bf16(w + 32), acc[t], 0, 0, 0);
         acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_from_bf16(&As[16 * t + r][8 * g]), frag_from_bf16(w + 64), acc[t], 0, 0, 0);
         acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_from_bf16(&As[16 * t + r][32 + 8 * g]), frag_from_bf16(w + 96), acc[t], 0, 0, 0);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) hold[t][q] = H[(size_t)(nb0 + 16 * t + 4 * g + q) * HID + col];
+        for (int q = 0; q < 4; ++q) hold[t][q] = H[(size_t)(nb0 + 16 * t + 4 * g + q) * ldh + col];
     }
     __syncthreads();  // every wavefront has read the block's rows of H before they change
     const float bu = W.bu[col];
@@ -702,8 +807,10 @@ __global__ __launch_bounds__(256, 4) void k_gnn_layer(
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int row = 16 * t + 4 * g + q;
-            const float h = hold[t][q] + fmaxf(acc[t][q] + bu, 0.f);
-            if (W.WaT) H[(size_t)(nb0 + row) * HID + col] = h;  // (the decoder is the last reader)
+            const float z = acc[t][q] + bu;
+            const float h = hold[t][q] + fmaxf(z, 0.f);
+            if constexpr (TRAIN) K.Z[(size_t)(nb0 + row) * HID + col] = z;
+            if (TRAIN || W.WaT) Ho[(size_t)(nb0 + row) * ldo + col] = h;  // (the decoder is the last reader)
             Hb[row][col] = (uint16_t)bf16_pair(h, 0.f);
         }
     __syncthreads();
@@ -739,7 +846,11 @@ __global__ __launch_bounds__(256, 4) void k_gnn_layer(
                                                           f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
         d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_from_bf16(&Hb[16 * t + r][32 + 8 * g]), frag_from_bf16(wo + 32), d, 0, 0, 0);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) D1[(16 * t + 4 * g + q) * (HID + 4) + col] = fmaxf(d[q] + bo, 0.f);
+        for (int q = 0; q < 4; ++q) {
+            const float v = fmaxf(d[q] + bo, 0.f);
+            D1[(16 * t + 4 * g + q) * (HID + 4) + col] = v;
+            if constexpr (TRAIN) K.D1[(size_t)(nb0 + 16 * t + 4 * g + q) * HID + col] = v;
+        }
     }
     __syncthreads();
     const int node = threadIdx.x / NOUT, c = threadIdx.x % NOUT;
@@ -749,43 +860,261 @@ __global__ __launch_bounds__(256, 4) void k_gnn_layer(
     Y[(size_t)(nb0 + node) * NOUT + c] = y;
 }
 
-// Backward of the messages: dM_e = dA_i [pre_e > 0]; dP_i = sum_e dM_e;
-// wsum_i = sum over wall edges of dM_e (for qw).
-__global__ __launch_bounds__(256) void k_gnn_msg_bwd(int N, const int32_t* __restrict__ eoff,
-                                                     const int32_t* __restrict__ edst, const float* __restrict__ pre,
-                                                     const float* __restrict__ dA, int ldda, float* __restrict__ dM,
-                                                     float* __restrict__ dP, float* __restrict__ wsum)
+// ---------------------------------------------------------------------
+// Backward of the edges. dM_e = dA_src(e) where message e was positive, else
+// 0: it is formed from the sign bits and the source's row of dA wherever it
+// is needed, so that no E x 64 array is stored (dM, R, E0, dE0 and the
+// pre-activations were 256 bytes an edge each, written once and read up to
+// four times). E0 is formed again from the edge features.
+
+// A lane's value where its bit of the (uniform) word m is set, else 0.
+__device__ __forceinline__ float where_bit(unsigned long long m, float v)
 {
-    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i >= N) return;
-    const int f = threadIdx.x & 63;
-    const float da = dA[(size_t)i * ldda + f];
-    float sp = 0.f, sw = 0.f;
-    for (int e = eoff[i]; e < eoff[i + 1]; ++e) {
-        const float dm = pre[(size_t)e * HID + f] > 0.f ? da : 0.f;
-        dM[(size_t)e * HID + f] = dm;
-        sp += dm;
-        if (edst[e] < 0) sw += dm;
-    }
-    dP[(size_t)i * HID + f] = sp;
-    wsum[(size_t)i * HID + f] = sw;
+    return __builtin_amdgcn_inverse_ballot_w64(m) ? v : 0.f;
 }
 
-// dQ_j = sum of dM over the inner edges that end at j, gathered through the
-// reverse of j's own inner edges.
-__global__ __launch_bounds__(256) void k_gnn_dq(int N, const int32_t* __restrict__ eoff,
-                                                const int32_t* __restrict__ edst, const int32_t* __restrict__ erev,
-                                                const float* __restrict__ dM, float* __restrict__ dQ)
+// Word k of a wavefront's 64 words.
+__device__ __forceinline__ unsigned long long lane_word(unsigned long long v, int k)
 {
-    const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (j >= N) return;
-    const int f = threadIdx.x & 63;
-    float s = 0.f;
-    for (int e = eoff[j]; e < eoff[j + 1]; ++e) {
-        const int rv = erev[e];
-        if (edst[e] >= 0 && rv >= 0) s += dM[(size_t)rv * HID + f];
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, k), hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), k);
+    return ((unsigned long long)hi << 32) | lo;
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const float* p, int N)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)((unsigned)N * ROW_BYTES), 0x00020000);
+}
+// The lane's column of the row at byte offset `off` (uniform).
+__device__ __forceinline__ float row_load(__amdgpu_buffer_rsrc_t p, int off)
+{
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(p, (int)(threadIdx.x & 63) * 4, off, 0));
+}
+
+// Per node i (one wavefront, lane = feature): dP_i = sum_e dM_e,
+// wsum_i = sum over wall edges of dM_e (for qw), and dQ_i = sum of dM over the
+// inner edges that end at i, through the reverse of its own inner edges.
+__global__ __launch_bounds__(256) void k_gnn_node_bwd(int N, const int32_t* __restrict__ eoff,
+                                                      const int32_t* __restrict__ edst,
+                                                      const int32_t* __restrict__ erev,
+                                                      const unsigned long long* __restrict__ mask,
+                                                      const float* __restrict__ dA, float* __restrict__ dP,
+                                                      float* __restrict__ dQ, float* __restrict__ wsum)
+{
+    const int i = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (i >= N) return;
+    const int lane = threadIdx.x & 63;
+    const __amdgpu_buffer_rsrc_t rows = rows_rsrc(dA, N);
+    const float da = dA[(size_t)i * HID + lane];
+    const int e0 = eoff[i], e1 = eoff[i + 1];
+    float sp = 0.f, sw = 0.f, sq = 0.f;
+    for (int eb = e0; eb < e1; eb += 64) {
+        unsigned long long own = 0ull, rev = 0ull;
+        int at = 0, d = 0;
+        if (eb + lane < e1) {
+            const int e = eb + lane;
+            own = mask[e];
+            d = edst[e];
+            const int rv = erev[e];
+            if (d >= 0 && rv >= 0) {
+                rev = mask[rv];
+                at = (int)((unsigned)d * ROW_BYTES);
+            }
+        }
+        const unsigned long long wall = __ballot(d < 0);
+        const int n = min(64, e1 - eb);
+        for (int k = 0; k < n; k += 8) {  // (words past n are 0)
+            float dj[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) dj[u] = row_load(rows, __builtin_amdgcn_readlane(at, k + u));
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const float dm = where_bit(lane_word(own, k + u), da);
+                sp += dm;
+                if ((wall >> (k + u)) & 1ull) sw += dm;
+                sq += where_bit(lane_word(rev, k + u), dj[u]);
+            }
+        }
     }
-    dQ[(size_t)j * HID + f] = s;
+    dP[(size_t)i * HID + lane] = sp;
+    dQ[(size_t)i * HID + lane] = sq;
+    wsum[(size_t)i * HID + lane] = sw;
+}
+
+// Weight gradient of the edge product, dWc = E0^T dM over the edges [64 x 64]
+// in row blocks, as k_wgrad: E0 and dM of a step's edges are formed in
+// registers and staged transposed (E0 from the matrix cores with the edges as
+// rows, so that a lane holds four consecutive edges of one feature; dM with
+// one lane per feature, its row of dA under the edge's sign word).
+__global__ __launch_bounds__(256) void k_gnn_wgrad_edge(int E, int rows, int N, const float* __restrict__ G,
+                                                        const int32_t* __restrict__ esrc,
+                                                        const uint16_t* __restrict__ WeT, const float* __restrict__ be,
+                                                        const unsigned long long* __restrict__ mask,
+                                                        const float* __restrict__ dA, float* __restrict__ part)
+{
+    __shared__ __align__(16) uint16_t Xs[HID][WPAD];
+    __shared__ __align__(16) uint16_t Zs[HID][WPAD];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int r = lane & 15, g = lane >> 4;
+    const __amdgpu_buffer_rsrc_t drow = rows_rsrc(dA, N);
+    bf16x8 wef[4];
+    float bev[4];
+    f32x4 acc[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        wef[t] = frag_from_bf16(WeT + (size_t)(16 * t + r) * FPAD + 8 * g);
+        bev[t] = be[16 * t + r];
+        acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int r0 = blockIdx.x * rows, r1 = min(r0 + rows, E);
+    // this lane's edge of the wavefront's 16 (lanes r and r + 16 k alike)
+    unsigned long long m = 0ull;
+    int at = 0;
+    bf16x8 gf;
+    auto load = [&](int rb) __attribute__((always_inline)) {
+        const int e = rb + 16 * w + r;
+        const bool ok = e < r1;
+        m = ok ? mask[e] : 0ull;
+        at = ok ? esrc[e] : 0;
+        gf = frag_from_f32(G + (size_t)(ok ? e : r0) * EFEAT, ok && g == 0);
+    };
+    load(r0);
+    for (int rb = r0; rb < r1; rb += WROWS) {
+        float z[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) z[q] = row_load(drow, __builtin_amdgcn_readlane(at, q));
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const f32x4 a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf, wef[t], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            *(uint2*)&Xs[16 * t + r][16 * w + 4 * g] =
+                make_uint2(bf16_pair(fmaxf(a[0] + bev[t], 0.f), fmaxf(a[1] + bev[t], 0.f)),
+                           bf16_pair(fmaxf(a[2] + bev[t], 0.f), fmaxf(a[3] + bev[t], 0.f)));
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q) z[q] = where_bit(lane_word(m, q), z[q]);
+        store_rows16(&Zs[lane][16 * w], z);
+        __syncthreads();
+        if (rb + WROWS < r1) load(rb + WROWS);
+        wgrad_step<4>(Xs, Zs, w, r, g, acc);
+        __syncthreads();
+    }
+    float* out = part + (size_t)blockIdx.x * HID * HID;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) out[(size_t)(16 * t + 4 * g + q) * HID + 16 * w + r] = acc[t][q];
+}
+
+// Backward of the edge encoder in row blocks: dE0 = sum over the layers (last
+// first) of dM_l Wc_l^T, dZe = dE0 where E0 > 0, dWe = G^T dZe [FPAD x 64, the
+// rows past the features 0] and dbe = column sums of dZe, row by row.
+// Wavefront w computes feature columns 16 w .. 16 w + 15 of a step's 64 edges
+// and keeps its six weight fragments in registers; the rows of dM_l, formed
+// by the wavefront of their edges, go through LDS, one layer at a time.
+struct EncBwd {
+    const unsigned long long* mask[3];
+    const float* dA[3];
+    const uint16_t* WcN[3];
+};
+__global__ __launch_bounds__(256) void k_gnn_enc_bwd(int E, int rows, int N, const float* __restrict__ G,
+                                                     const int32_t* __restrict__ esrc,
+                                                     const uint16_t* __restrict__ WeT, const float* __restrict__ be,
+                                                     EncBwd B, float* __restrict__ part, float* __restrict__ bpart)
+{
+    __shared__ __align__(16) uint16_t Ds[WROWS][HID + 8];  // dM_l, edge rows
+    __shared__ __align__(16) uint16_t Xs[16][WPAD];        // features (8 used), transposed
+    __shared__ __align__(16) uint16_t Zs[HID][WPAD];       // dZe, transposed
+    __shared__ float Zf[WROWS][HID];                       // dZe, FP32
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int r = lane & 15, g = lane >> 4;
+    const int col = 16 * w + r;
+    const bf16x8 wef = frag_from_bf16(WeT + (size_t)col * FPAD + 8 * g);
+    const float bev = be[col];
+    bf16x8 wcf[3][2];
+#pragma unroll
+    for (int l = 0; l < 3; ++l)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) wcf[l][k] = frag_from_bf16(B.WcN[l] + (size_t)col * HID + 32 * k + 8 * g);
+    for (int k = threadIdx.x; k < 16 * WPAD; k += 256) (&Xs[0][0])[k] = 0;
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    float bsum = 0.f;
+    const int r0 = blockIdx.x * rows, r1 = min(r0 + rows, E);
+    __syncthreads();
+    for (int rb = r0; rb < r1; rb += WROWS) {
+        const int e = rb + 16 * w + r;
+        const bool ok = e < r1;
+        const int at = ok ? esrc[e] : 0;
+        unsigned long long m[3];
+#pragma unroll
+        for (int l = 0; l < 3; ++l) m[l] = ok ? B.mask[l][e] : 0ull;
+        // E0 of the step's edges: its sign, in the layout of the sums below
+        uint32_t pos = 0;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int et = rb + 16 * t + r;
+            const bf16x8 gf = frag_from_f32(G + (size_t)min(et, r1 - 1) * EFEAT, et < r1 && g == 0);
+            if (t == w && g == 0) {  // this wavefront's edges: their features, transposed
+                Frag f;
+                f.v = gf;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    Xs[2 * k][16 * w + r] = (uint16_t)f.u[k];
+                    Xs[2 * k + 1][16 * w + r] = (uint16_t)(f.u[k] >> 16);
+                }
+            }
+            const f32x4 a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf, wef, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) pos |= (a[q] + bev > 0.f ? 1u : 0u) << (4 * t + q);
+        }
+        f32x4 sum[4];
+#pragma unroll
+        for (int ll = 0; ll < 3; ++ll) {
+            const int l = 2 - ll;
+            const __amdgpu_buffer_rsrc_t drow = rows_rsrc(B.dA[l], N);
+            float z[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) z[q] = row_load(drow, __builtin_amdgcn_readlane(at, q));
+            if (ll) __syncthreads();  // the previous layer's rows have been read
+#pragma unroll
+            for (int q = 0; q < 16; ++q)
+                Ds[16 * w + q][lane] = (uint16_t)bf16_pair(where_bit(lane_word(m[l], q), z[q]), 0.f);
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+                    a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag_from_bf16(&Ds[16 * t + r][32 * k + 8 * g]), wcf[l][k],
+                                                                a, 0, 0, 0);
+                if (ll == 0) sum[t] = a;
+                else sum[t] = sum[t] + a;
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            float v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                v[q] = (pos >> (4 * t + q)) & 1u ? sum[t][q] : 0.f;
+                Zf[16 * t + 4 * g + q][col] = v[q];
+            }
+            *(uint2*)&Zs[col][16 * t + 4 * g] = make_uint2(bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3]));
+        }
+        __syncthreads();
+        wgrad_step<1>(Xs, Zs, w, r, g, &acc);
+        if (threadIdx.x < HID) {
+            const int n = min(WROWS, r1 - rb);
+#pragma unroll 16
+            for (int q = 0; q < n; ++q) bsum += Zf[q][threadIdx.x];
+        }
+        __syncthreads();
+    }
+    float* out = part + (size_t)blockIdx.x * FPAD * HID;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        out[(size_t)(4 * g + q) * HID + col] = acc[q];
+        out[(size_t)(16 + 4 * g + q) * HID + col] = 0.f;
+    }
+    if (threadIdx.x < HID) bpart[(size_t)blockIdx.x * HID + threadIdx.x] = bsum;
 }
 
 // out = src where mask > 0, else 0 (row strides given).
@@ -879,7 +1208,18 @@ __global__ __launch_bounds__(256) void k_gnn_out_wgrad(int N, int rows, const fl
     float s = 0.f;
     if (t < HID * NOUT) {
         const int k = t / NOUT, c = t % NOUT;
-        for (int r = r0; r < r1; ++r) s += D1[(size_t)r * HID + k] * dY[(size_t)r * NOUT + c];
+        int r = r0;
+        for (; r + 16 <= r1; r += 16) {  // 32 loads in flight
+            float a[16], b[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                a[q] = D1[(size_t)(r + q) * HID + k];
+                b[q] = dY[(size_t)(r + q) * NOUT + c];
+            }
+#pragma unroll
+            for (int q = 0; q < 16; ++q) s += a[q] * b[q];
+        }
+        for (; r < r1; ++r) s += D1[(size_t)r * HID + k] * dY[(size_t)r * NOUT + c];
     } else {
         const int c = t - HID * NOUT;
         for (int r = r0; r < r1; ++r) s += dY[(size_t)r * NOUT + c];

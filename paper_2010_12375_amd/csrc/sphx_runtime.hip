@@ -1907,15 +1907,15 @@ struct Engine final : EngineBase {
         uint16_t *wt = nullptr, *wn = nullptr;
         int Ncap = 0;
         long long Ecap = 0;
-        bool Ecap_train = false, Ncap_train = false;
+        bool Efull = false, Ncap_train = false;
         std::vector<void*> fixed, nodes, edges;
         int32_t *ecount = nullptr, *eoff = nullptr, *bsumN = nullptr, *edst = nullptr, *erev = nullptr,
                 *esrc = nullptr;
-        bool fused = true;  // inference forward with the fused layer kernel (else edge activations in HBM)
         float *F = nullptr, *X[3] = {}, *Hs = nullptr, *Z[3] = {}, *P = nullptr, *Q[2] = {}, *D1 = nullptr,
               *Y = nullptr, *T = nullptr, *dY = nullptr;
-        float *dH = nullptr, *dZ = nullptr, *dA = nullptr, *dPb = nullptr, *dQb = nullptr, *wsum = nullptr;
-        float *G = nullptr, *E0 = nullptr, *R = nullptr, *pre[3] = {}, *dM = nullptr, *dE0 = nullptr;
+        float *dH = nullptr, *dZ = nullptr, *dA[3] = {}, *dPb = nullptr, *dQb = nullptr, *wsum = nullptr;
+        float *G = nullptr, *E0 = nullptr, *R = nullptr;  // E0, R: the unfused forward (profiling) only
+        unsigned long long* mask[3] = {};  // per edge and layer: the sign bits of its message
         float *part = nullptr, *bpart = nullptr;
         double *lpart = nullptr, *dtc = nullptr, *tmax = nullptr;
         int32_t* accept = nullptr;
@@ -1974,7 +1974,7 @@ struct Engine final : EngineBase {
         if (train) {
             RETCHK(dalloc(A, gn.dH, n64));
             RETCHK(dalloc(A, gn.dZ, n64));
-            RETCHK(dalloc(A, gn.dA, n64));
+            for (float*& q : gn.dA) RETCHK(dalloc(A, q, n64));
             RETCHK(dalloc(A, gn.dPb, n64));
             RETCHK(dalloc(A, gn.dQb, n64));
             RETCHK(dalloc(A, gn.wsum, n64));
@@ -1987,30 +1987,28 @@ struct Engine final : EngineBase {
         return SPHX_OK;
     }
 
-    int gnn_edges_alloc(long long E, bool train)
+    // Edge buffers for E edges; `full`: also the activations of the unfused
+    // forward (padded feature rows, E0 and R).
+    int gnn_edges_alloc(long long E, bool full)
     {
         E = std::max(E, 1LL);
-        if (gn.Ecap >= E && (!train || gn.Ecap_train)) return SPHX_OK;
+        if (gn.Ecap >= E && (!full || gn.Efull)) return SPHX_OK;
         HIPCHK(hipStreamSynchronize(s));
         free_list(gn.edges);
+        gn.Ecap = 0;
         auto& A = gn.edges;
         const long long cap = E + E / 8 + 1024;
-        const size_t e64 = (size_t)cap * gnn::HID;
         RETCHK(dalloc(A, gn.edst, cap));
         RETCHK(dalloc(A, gn.erev, cap));
         RETCHK(dalloc(A, gn.esrc, cap));
-        RETCHK(dalloc(A, gn.G, (size_t)cap * gnn::FPAD));
-        RETCHK(dalloc(A, gn.E0, e64));
-        RETCHK(dalloc(A, gn.R, e64));
-        if (train) {
-            for (int l = 0; l < 3; ++l) RETCHK(dalloc(A, gn.pre[l], e64));
-            RETCHK(dalloc(A, gn.dM, e64));
-            RETCHK(dalloc(A, gn.dE0, e64));
-        } else {
-            for (int l = 0; l < 3; ++l) gn.pre[l] = nullptr;
+        RETCHK(dalloc(A, gn.G, (size_t)cap * (full ? gnn::FPAD : gnn::EFEAT)));
+        for (auto*& m : gn.mask) RETCHK(dalloc(A, m, cap));
+        if (full) {
+            RETCHK(dalloc(A, gn.E0, (size_t)cap * gnn::HID));
+            RETCHK(dalloc(A, gn.R, (size_t)cap * gnn::HID));
         }
         gn.Ecap = cap;
-        gn.Ecap_train = train;
+        gn.Efull = full;
         return SPHX_OK;
     }
 
@@ -2069,12 +2067,12 @@ struct Engine final : EngineBase {
         return SPHX_OK;
     }
 
-    // The CSR graph and the features of the current configuration (with
-    // `compact`: the edge features alone per row, source indices, no reverse
-    // edges, for the fused inference layer).
-    int gnn_graph(bool train, bool compact = false)
+    // The CSR graph and the features of the current configuration: compact
+    // feature rows and the reverse edges for training, or (`unfused`) padded
+    // rows for the encoder product of the unfused forward.
+    int gnn_graph(bool unfused)
     {
-        RETCHK(gnn_nodes(train));
+        RETCHK(gnn_nodes(true));
         const int N = ntot;
         gnn::k_gnn_count<real><<<nblk(N), BLOCK, 0, s>>>(dP, tcase, ntiles, ncnt, wcnt, gn.ecount);
         const int nb = (N + SCAN_TILE - 1) / SCAN_TILE;
@@ -2086,17 +2084,21 @@ struct Engine final : EngineBase {
         HIPCHK(hipMemcpyAsync(&etot, gn.eoff + N, sizeof(int32_t), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         gn.E = etot;
-        RETCHK(gnn_edges_alloc(gn.E, train));
-        if constexpr (D == 2) {
-            by_lanes([&](auto t) {
-                gnn::k_gnn_edges<real, decltype(t)::value><<<nblk(N), BLOCK, 0, s>>>(
-                    dP, tcase, ntiles, gn.eoff, nbr, ncnt, wnb, wcnt, geo[cur], wgeo, st[cur], gn.edst,
-                    compact ? nullptr : gn.erev, compact ? gn.esrc : nullptr, gn.G, compact ? gnn::EFEAT : gnn::FPAD,
-                    gn.F);
-            });
-        }
+        RETCHK(gnn_edges_alloc(gn.E, unfused));
+        launch_edges(unfused);
         HIPCHK(hipGetLastError());
         return SPHX_OK;
+    }
+
+    void launch_edges(bool unfused)
+    {
+        if constexpr (D == 2) {
+            by_lanes([&](auto t) {
+                gnn::k_gnn_edges<real, decltype(t)::value><<<nblk((long long)ntot * gnn::EL), BLOCK, 0, s>>>(
+                    dP, tcase, ntot, gn.eoff, nbr, ncnt, wnb, wcnt, geo[cur], wgeo, st[cur], gn.edst,
+                    unfused ? nullptr : gn.erev, gn.esrc, gn.G, unfused ? gnn::FPAD : gnn::EFEAT, gn.F);
+            });
+        }
     }
 
     template <int K, int EPI>
@@ -2107,17 +2109,31 @@ struct Engine final : EngineBase {
         gnn::k_gemm64<K, EPI><<<(int)((M + 63) / 64), 256, 0, s>>>((int)M, A, lda, Bt, bias, Cm, ldc, C2, ldc2);
     }
 
+    // Rows per block of a weight gradient over M rows (the partial sums'
+    // split, at most PART_BLOCKS blocks).
+    static int part_rows(long long M)
+    {
+        const int rows = (int)((M + PART_BLOCKS - 1) / PART_BLOCKS);
+        return std::max(256, (rows + 31) / 32 * 32);
+    }
+
+    // out (len) and optionally out2 (len2) from nb blocks' partials in gn.part
+    // and gn.bpart.
+    void reduce_parts(int nb, int len, float* out, int len2 = 0, float* out2 = nullptr)
+    {
+        const int n1 = (len + gnn::RCOLS - 1) / gnn::RCOLS, n2 = out2 ? (len2 + gnn::RCOLS - 1) / gnn::RCOLS : 0;
+        gnn::k_reduce_parts<<<n1 + n2, 256, 0, s>>>(nb, n1, len, gn.part, out, len2, gn.bpart, out2);
+    }
+
     // dW (KIN x 64) and optionally db (64) from X^T dZ over M rows.
     template <int KIN>
     void wgrad(long long M, const float* X, int ldx, const float* dZ, int ldz, float* dW, float* db)
     {
         if (M <= 0) return;
-        int rows = (int)((M + PART_BLOCKS - 1) / PART_BLOCKS);
-        rows = std::max(256, (rows + 31) / 32 * 32);
+        const int rows = part_rows(M);
         const int nb = (int)((M + rows - 1) / rows);
-        gnn::k_wgrad<KIN><<<nb, 256, 0, s>>>((int)M, rows, X, ldx, dZ, ldz, gn.part, gn.bpart);
-        gnn::k_reduce_parts<<<(KIN * gnn::HID + 255) / 256, 256, 0, s>>>(nb, KIN * gnn::HID, gn.part, dW, 0);
-        if (db) gnn::k_reduce_parts<<<1, 256, 0, s>>>(nb, gnn::HID, gn.bpart, db, 0);
+        gnn::k_wgrad<KIN><<<nb, 256, 0, s>>>((int)M, rows, X, ldx, dZ, ldz, gn.part, db ? gn.bpart : nullptr);
+        reduce_parts(nb, KIN * gnn::HID, dW, gnn::HID, db);
     }
 
     void elem64(long long M, const float* src, int lds, const float* mask, int ldm, float* out, int ldo)
@@ -2130,38 +2146,68 @@ struct Engine final : EngineBase {
             gnn::k_copy64<<<(int)((n + 255) / 256), 256, 0, s>>>((int)M, src, lds, out, ldo);
     }
 
-    // One layer of the inference forward, Q in gn.Q[l & 1]. 32 nodes per block
+    // One layer of the forward pass, Q in gn.Q[l & 1]. 32 nodes per block
     // once that fills the GPU several times over (half the weight loads per
     // node), else 16, which shortens each wavefront's chain of edge tiles.
-    void infer_layer(int l)
+    void layer(int l, bool train)
     {
         const GnnLayout& L = gn.L;
         float* p = gn.p;
         const int N = ntot;
         const bool last = l == 2;
         const int n = last ? l : l + 1;
+        constexpr int H = gnn::HID;
         const gnn::LayerW W = {gn.wt + L.pWe, gn.wt + L.pWc[l], gn.wt + L.pWu[l], last ? nullptr : gn.wt + L.pWa[n],
                                gn.wt + L.pWb[n], gn.wt + L.pWo1, p + L.be, p + L.bu[l], p + L.bm[n], p + L.qw[n],
                                p + L.bo1, p + L.Wo2, p + L.bo2};
+        const gnn::LayerKeep K = {gn.eoff, gn.mask[l], gn.X[l], gn.Z[l], gn.D1};
         const int lt = ln == 2 ? 1 : ln == 4 ? 2 : 3;
+        // training keeps every layer's H (with its A, rows of 128)
+        const float* Hi = train ? gn.X[l] : gn.Hs;
+        float* Ho = train && !last ? gn.X[n] : gn.Hs;
         if constexpr (D == 2) {
-            auto go = [&](auto npw) {
+            auto go = [&](auto npw, auto tr) {
                 constexpr int NPW = decltype(npw)::value;
-                gnn::k_gnn_layer<real, NPW><<<N / (4 * NPW), 256, 0, s>>>(
-                    dP, tcase, N, lt, nbr, ncnt, wnb, wcnt, geo[cur], wgeo, st[cur], W, gn.Hs, gn.P, gn.Q[l & 1],
-                    gn.Q[1 - (l & 1)], gn.Y);
+                gnn::k_gnn_layer<real, NPW, decltype(tr)::value><<<N / (4 * NPW), 256, 0, s>>>(
+                    dP, tcase, N, lt, nbr, ncnt, wnb, wcnt, geo[cur], wgeo, st[cur], W, Hi, train ? 2 * H : H, Ho,
+                    train && !last ? 2 * H : H, gn.P, gn.Q[l & 1], gn.Q[1 - (l & 1)], gn.Y, K);
             };
-            if (N >= GNN_WIDE) go(std::integral_constant<int, 8>{});
-            else go(std::integral_constant<int, 4>{});
+            auto width = [&](auto tr) {
+                if (N >= GNN_WIDE) go(std::integral_constant<int, 8>{}, tr);
+                else go(std::integral_constant<int, 4>{}, tr);
+            };
+            if (train) width(std::true_type{});
+            else width(std::false_type{});
         }
     }
     static constexpr int GNN_WIDE = 1 << 16;
 
+    // The forward pass (with `train`, on the graph gnn_graph has made).
     int gnn_forward_impl(bool train)
     {
-        // inference: one kernel per layer, nothing per edge in HBM
-        if (!train && gn.fused) return gnn_forward_fused();
-        RETCHK(gnn_graph(train));
+        // rows are addressed with 32-bit byte offsets
+        if (ntot > (1 << 24) - 2) return ctx->fail(SPHX_ENOMEM, "too many particles for the surrogate");
+        RETCHK(gnn_nodes(train));
+        if (train) RETCHK(gnn_graph(false));
+        const GnnLayout& L = gn.L;
+        float* p = gn.p;
+        const int N = ntot;
+        constexpr int H = gnn::HID;
+        if constexpr (D == 2)
+            gnn::k_gnn_encode<real><<<N / 64, 256, 0, s>>>(dP, tcase, N, ncnt, wcnt, st[cur], gn.wt + L.pWn, p + L.bn,
+                                                           gn.wt + L.pWa[0], p + L.bm[0], gn.wt + L.pWb[0], p + L.qw[0],
+                                                           train ? gn.X[0] : gn.Hs, train ? 2 * H : H, gn.P, gn.Q[0]);
+        for (int l = 0; l < 3; ++l) layer(l, train);
+        HIPCHK(hipGetLastError());
+        gn.gen = conf_gen;
+        return SPHX_OK;
+    }
+
+    // The same forward with the edge activations and products through device
+    // memory, for gnn_profile's comparison.
+    int gnn_forward_unfused()
+    {
+        RETCHK(gnn_graph(true));
         const GnnLayout& L = gn.L;
         const int N = ntot;
         const long long E = gn.E;
@@ -2174,33 +2220,13 @@ struct Engine final : EngineBase {
             gemm<64, gnn::EPI_STORE>(N, gn.X[l], 2 * H, gn.wt + L.pWa[l], p + L.bm[l], gn.P, H);
             gemm<64, gnn::EPI_STORE>(N, gn.X[l], 2 * H, gn.wt + L.pWb[l], nullptr, gn.Q[0], H);
             gemm<64, gnn::EPI_STORE>(E, gn.E0, H, gn.wt + L.pWc[l], nullptr, gn.R, H);
-            gnn::k_gnn_msg<<<(N + 3) / 4, 256, 0, s>>>(N, gn.eoff, gn.edst, gn.P, gn.Q[0], gn.R, p + L.qw[l],
-                                                       train ? gn.pre[l] : nullptr, gn.X[l]);
+            gnn::k_gnn_msg<<<(N + 3) / 4, 256, 0, s>>>(N, gn.eoff, gn.edst, gn.P, gn.Q[0], gn.R, p + L.qw[l], gn.X[l]);
             gemm<128, gnn::EPI_RESID>(N, gn.X[l], 2 * H, gn.wt + L.pWu[l], p + L.bu[l], gn.Hs, H, gn.Z[l], H);
             if (l < 2) elem64(N, gn.Hs, H, nullptr, 0, gn.X[l + 1], 2 * H);
         }
         gemm<64, gnn::EPI_RELU>(N, gn.Hs, H, gn.wt + L.pWo1, p + L.bo1, gn.D1, H);
         gnn::k_gnn_out<<<nblk(N), BLOCK, 0, s>>>(N, gn.D1, p + L.Wo2, p + L.bo2, gn.Y);
         HIPCHK(hipGetLastError());
-        gn.gen = conf_gen;
-        return SPHX_OK;
-    }
-
-    int gnn_forward_fused()
-    {
-        // rows of Q are addressed with 32-bit byte offsets
-        if (ntot > (1 << 24) - 2) return ctx->fail(SPHX_ENOMEM, "too many particles for the surrogate");
-        RETCHK(gnn_nodes(false));
-        const GnnLayout& L = gn.L;
-        float* p = gn.p;
-        const int N = ntot;
-        if constexpr (D == 2)
-            gnn::k_gnn_encode<real><<<N / 64, 256, 0, s>>>(dP, tcase, N, ncnt, wcnt, st[cur], gn.wt + L.pWn, p + L.bn,
-                                                           gn.wt + L.pWa[0], p + L.bm[0], gn.wt + L.pWb[0], p + L.qw[0],
-                                                           gn.Hs, gn.P, gn.Q[0]);
-        for (int l = 0; l < 3; ++l) infer_layer(l);
-        HIPCHK(hipGetLastError());
-        gn.gen = conf_gen;
         return SPHX_OK;
     }
 
@@ -2216,37 +2242,45 @@ struct Engine final : EngineBase {
             const int rows = std::max(256, (N + PART_BLOCKS - 1) / PART_BLOCKS);
             const int nb = (N + rows - 1) / rows;
             gnn::k_gnn_out_wgrad<<<nb, 256, 0, s>>>(N, rows, gn.D1, gn.dY, gn.part);
-            gnn::k_reduce_parts<<<1, 256, 0, s>>>(nb, H * 3 + 3, gn.part, g + L.Wo2, 0);
+            reduce_parts(nb, H * 3 + 3, g + L.Wo2);
             const long long n = (long long)N * H;
             gnn::k_gnn_out_bwd<<<(int)((n + 255) / 256), 256, 0, s>>>(N, gn.D1, gn.dY, p + L.Wo2, gn.dZ);
         }
         wgrad<64>(N, gn.Hs, H, gn.dZ, H, g + L.Wo1, g + L.bo1);
         gemm<64, gnn::EPI_STORE>(N, gn.dZ, H, gn.wn + L.pWo1, nullptr, gn.dH, H);
+        const int erows = part_rows(E), enb = (int)((E + erows - 1) / erows);
         for (int l = 2; l >= 0; --l) {
             elem64(N, gn.dH, H, gn.Z[l], H, gn.dZ, H);
             wgrad<128>(N, gn.X[l], 2 * H, gn.dZ, H, g + L.Wu[l], g + L.bu[l]);
             gemm<64, gnn::EPI_ACCUM>(N, gn.dZ, H, gn.wn + L.pWu[l], nullptr, gn.dH, H);
-            gemm<64, gnn::EPI_STORE>(N, gn.dZ, H, gn.wn + L.pWu[l] + 64 * H, nullptr, gn.dA, H);
-            gnn::k_gnn_msg_bwd<<<(N + 3) / 4, 256, 0, s>>>(N, gn.eoff, gn.edst, gn.pre[l], gn.dA, H, gn.dM, gn.dPb,
-                                                           gn.wsum);
-            gnn::k_gnn_dq<<<(N + 3) / 4, 256, 0, s>>>(N, gn.eoff, gn.edst, gn.erev, gn.dM, gn.dQb);
+            gemm<64, gnn::EPI_STORE>(N, gn.dZ, H, gn.wn + L.pWu[l] + 64 * H, nullptr, gn.dA[l], H);
+            gnn::k_gnn_node_bwd<<<(N + 3) / 4, 256, 0, s>>>(N, gn.eoff, gn.edst, gn.erev, gn.mask[l], gn.dA[l], gn.dPb,
+                                                            gn.dQb, gn.wsum);
             {
                 const int rows = std::max(256, (N + PART_BLOCKS - 1) / PART_BLOCKS);
                 const int nb = (N + rows - 1) / rows;
-                gnn::k_colsum64<<<nb, 64, 0, s>>>(N, rows, gn.wsum, H, gn.bpart);
-                gnn::k_reduce_parts<<<1, 256, 0, s>>>(nb, H, gn.bpart, g + L.qw[l], 0);
+                gnn::k_colsum64<<<nb, 64, 0, s>>>(N, rows, gn.wsum, H, gn.part);
+                reduce_parts(nb, H, g + L.qw[l]);
             }
             wgrad<64>(N, gn.X[l], 2 * H, gn.dPb, H, g + L.Wa[l], g + L.bm[l]);
             wgrad<64>(N, gn.X[l], 2 * H, gn.dQb, H, g + L.Wb[l], nullptr);
-            wgrad<64>(E, gn.E0, H, gn.dM, H, g + L.Wc[l], nullptr);
+            if (E > 0) {
+                gnn::k_gnn_wgrad_edge<<<enb, 256, 0, s>>>((int)E, erows, N, gn.G, gn.esrc, gn.wt + L.pWe, p + L.be,
+                                                          gn.mask[l], gn.dA[l], gn.part);
+                reduce_parts(enb, H * H, g + L.Wc[l]);
+            }
             gemm<64, gnn::EPI_ACCUM>(N, gn.dPb, H, gn.wn + L.pWa[l], nullptr, gn.dH, H);
             gemm<64, gnn::EPI_ACCUM>(N, gn.dQb, H, gn.wn + L.pWb[l], nullptr, gn.dH, H);
-            if (l == 2) gemm<64, gnn::EPI_STORE>(E, gn.dM, H, gn.wn + L.pWc[l], nullptr, gn.dE0, H);
-            else gemm<64, gnn::EPI_ACCUM>(E, gn.dM, H, gn.wn + L.pWc[l], nullptr, gn.dE0, H);
         }
-        // encoders (dM is free again: it takes dZe)
-        elem64(E, gn.dE0, H, gn.E0, H, gn.dM, H);
-        wgrad<32>(E, gn.G, 32, gn.dM, H, g + L.We, g + L.be);
+        // encoders
+        if (E > 0) {
+            const gnn::EncBwd B = {{gn.mask[0], gn.mask[1], gn.mask[2]},
+                                   {gn.dA[0], gn.dA[1], gn.dA[2]},
+                                   {gn.wn + L.pWc[0], gn.wn + L.pWc[1], gn.wn + L.pWc[2]}};
+            gnn::k_gnn_enc_bwd<<<enb, 256, 0, s>>>((int)E, erows, N, gn.G, gn.esrc, gn.wt + L.pWe, p + L.be, B, gn.part,
+                                                   gn.bpart);
+            reduce_parts(enb, gnn::FPAD * H, g + L.We, H, g + L.be);
+        }
         elem64(N, gn.dH, H, gn.X[0], 2 * H, gn.dZ, H);
         wgrad<32>(N, gn.F, 32, gn.dZ, H, g + L.Wn, g + L.bn);
         HIPCHK(hipGetLastError());
@@ -2340,21 +2374,18 @@ struct Engine final : EngineBase {
         constexpr int H = gnn::HID;
         float* p = gn.p;
         auto whole = [&](bool fused, double* out) {
-            const bool keep = gn.fused;
-            gn.fused = fused;
             hipEvent_t ev[2];
             HIPCHK(hipEventCreate(&ev[0]));
             HIPCHK(hipEventCreate(&ev[1]));
             HIPCHK(hipEventRecord(ev[0], s));
             int rc = SPHX_OK;
-            for (int r = 0; r < reps && rc == SPHX_OK; ++r) rc = gnn_forward_impl(false);
+            for (int r = 0; r < reps && rc == SPHX_OK; ++r) rc = fused ? gnn_forward_impl(false) : gnn_forward_unfused();
             HIPCHK(hipEventRecord(ev[1], s));
             HIPCHK(hipEventSynchronize(ev[1]));
             float t = 0.f;
             HIPCHK(hipEventElapsedTime(&t, ev[0], ev[1]));
             (void)hipEventDestroy(ev[0]);
             (void)hipEventDestroy(ev[1]);
-            gn.fused = keep;
             *out = (double)t / reps;
             return rc;
         };
@@ -2363,21 +2394,14 @@ struct Engine final : EngineBase {
         const long long E = gn.E;
         RETCHK(time_launches(reps, &ms[5], [&] { gemm<64, gnn::EPI_STORE>(E, gn.E0, H, gn.wt + L.pWc[0], nullptr, gn.R, H); }));
         RETCHK(time_launches(reps, &ms[6], [&] {
-            gnn::k_gnn_msg<<<(N + 3) / 4, 256, 0, s>>>(N, gn.eoff, gn.edst, gn.P, gn.Q[0], gn.R, p + L.qw[0], nullptr,
+            gnn::k_gnn_msg<<<(N + 3) / 4, 256, 0, s>>>(N, gn.eoff, gn.edst, gn.P, gn.Q[0], gn.R, p + L.qw[0],
                                                        gn.X[0]);
         }));
         // the fused forward (the default)
         RETCHK(whole(true, &ms[3]));
-        RETCHK(time_launches(reps, &ms[0], [&] { infer_layer(0); }));
-        RETCHK(time_launches(reps, &ms[1], [&] {
-            if constexpr (D == 2) {
-                by_lanes([&](auto t) {
-                    gnn::k_gnn_edges<real, decltype(t)::value><<<nblk(N), BLOCK, 0, s>>>(
-                        dP, tcase, ntiles, gn.eoff, nbr, ncnt, wnb, wcnt, geo[cur], wgeo, st[cur], gn.edst, nullptr,
-                        gn.esrc, gn.G, gnn::EFEAT, gn.F);
-                });
-            }
-        }));
+        RETCHK(time_launches(reps, &ms[0], [&] { layer(0, false); }));
+        RETCHK(gnn_graph(false));
+        RETCHK(time_launches(reps, &ms[1], [&] { launch_edges(false); }));
         RETCHK(time_launches(reps, &ms[2], [&] {
             gemm<128, gnn::EPI_STORE>(N, gn.X[0], 2 * H, gn.wt + L.pWu[0], p + L.bu[0], gn.Z[0], H);
         }));

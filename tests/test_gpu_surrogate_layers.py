@@ -7,6 +7,7 @@ import math
 import numpy as np
 import pytest
 
+from oracle import gnn_oracle as G
 from paper_2010_12375_amd import gnn_inputs as gi
 from paper_2010_12375_amd import sphx
 from paper_2010_12375_amd import workloads as wl
@@ -67,3 +68,36 @@ def test_few_and_isolated_particles(n):
     # one rounding flip moves an output by about 2^-8 of itself (test_gpu_surrogate.py)
     assert np.abs(s.gnn_output() - Yo).max() <= 8 * 2.0 ** -8 * rms
     s.close()
+
+
+def _row(n):
+    case = wl.config_small(5)
+    dp = case.dp
+    x = np.column_stack([(np.arange(n) + 0.5) * dp, np.full(n, 0.5 * dp)])
+    x[4::5, 1] = 1.0 + 0.5 * np.arange(len(x[4::5]))[: len(x[4::5])] % 4.0
+    case.fluid_pos = x
+    return case
+
+
+@pytest.mark.parametrize("case,tol", [(_row(3), 8 * 2.0 ** -8), (_row(65), 8 * 2.0 ** -8),
+                                      (wl.dam_break_2d(0.0115, seed=6, precision=sphx.SPHX_FP32), 5e-3)],
+                         ids=["3", "65", "15k"])
+def test_training_gradients_at_ragged_sizes(case, tol):
+    """Edge counts below one step of 64, not a multiple of it, and beyond 256
+    rows a block (there: 320, a half step at the end). Tolerances: one
+    rounding flip (8 x 2^-8, test_gpu_surrogate.py) where a tensor's norm
+    comes from few particles, that file's 5e-3 at 15 000."""
+    st = developed_state(case, seed=6)
+    params = gi.init_params(24)
+    T = np.random.Generator(np.random.PCG64(98)).normal(0, 1, (case.n_fluid, 3))
+    g, Yo, cache = oracle_forward(case, st, params)
+    _, dY = G.loss_grad(Yo, T)
+    grad_o = G.backward(params.astype(np.float64), g, cache, dY, emu=True)
+    s = gpu_sim([case], [st], sphx.SPHX_FP32, params)
+    s.gnn_set_target(T)
+    s.gnn_train_step(1e-3)
+    pg, names = G.unpack(s.gnn_get_grad().astype(np.float64))
+    po, _ = G.unpack(grad_o)
+    s.close()
+    for n in names:
+        assert np.linalg.norm(pg[n] - po[n]) <= tol * np.linalg.norm(po[n]) + 1e-12, n
