@@ -786,11 +786,19 @@ struct Engine final : EngineBase {
         std::memset(&hctrl[c], 0, sizeof(Ctrl));
         RETCHK(push_ctrl());
         if (n > 0) {
-            k_vmax<D, real><<<nblk(ntot), BLOCK, 0, s>>>(dP, tcase, ntiles, c, nullptr, ctrl, st[cur]);
-            k_vmax_fin<real><<<(C + 63) / 64, 64, 0, s>>>(ctrl, C, c, nullptr);
+            enqueue_vmax(c, nullptr);
             HIPCHK(hipGetLastError());
         }
         return sync_ctrl();
+    }
+
+    // |v|max of case `only` (all: < 0; with a mask, of the cases it selects)
+    // into the control blocks.
+    void enqueue_vmax(int only, const int32_t* mask)
+    {
+        const int waves = (ntiles + VMAX_TILES - 1) / VMAX_TILES;
+        k_vmax<D, real><<<(waves * 64 + BLOCK - 1) / BLOCK, BLOCK, 0, s>>>(dP, tcase, ntiles, only, mask, vslot, st[cur]);
+        k_vmax_fin<real><<<C, 64, 0, s>>>(ctrl, vslot, only, mask);
     }
 
     int set_walls(int c, int64_t n, const double* pos, const double* nrm) override
@@ -1221,8 +1229,7 @@ struct Engine final : EngineBase {
         RETCHK(check_case(c));
         if (hP[c].nf == 0) return ctx->fail(SPHX_ESTATE, case_tag(c) + "no fluid particles");
         RETCHK(ensure_layout());
-        k_vmax<D, real><<<nblk(ntot), BLOCK, 0, s>>>(dP, tcase, ntiles, c, nullptr, ctrl, st[cur]);
-        k_vmax_fin<real><<<(C + 63) / 64, 64, 0, s>>>(ctrl, C, c, nullptr);
+        enqueue_vmax(c, nullptr);
         HIPCHK(hipGetLastError());
         RETCHK(sync_ctrl());
         const KP<real>& P = hP[c];
@@ -2485,8 +2492,7 @@ struct Engine final : EngineBase {
                 RETCHK(enqueue_rebuild(0, cur));
                 cur ^= 1;
                 ++conf_gen;
-                k_vmax<D, real><<<nblk(ntot), BLOCK, 0, s>>>(dP, tcase, ntiles, -1, gn.accept, ctrl, st[cur]);
-                k_vmax_fin<real><<<(C + 63) / 64, 64, 0, s>>>(ctrl, C, -1, gn.accept);
+                enqueue_vmax(-1, gn.accept);
                 HIPCHK(hipGetLastError());
                 RETCHK(sync_ctrl());
             }
