@@ -184,6 +184,7 @@ struct Engine final : EngineBase {
     uint32_t* nbr = nullptr;
     int32_t* ncnt = nullptr;
     uint32_t* wnb = nullptr;
+    real* dsum = nullptr;     // per particle: summed density deviation of the configuration
     int32_t* wcnt = nullptr;
     int32_t *key = nullptr, *rank = nullptr, *perm = nullptr;
     int32_t *cnt = nullptr, *fstart = nullptr, *bsum = nullptr;
@@ -663,6 +664,7 @@ struct Engine final : EngineBase {
         RETCHK(dalloc(L, ncnt, n));
         RETCHK(dalloc(L, wnb, (size_t)maxw * n));
         RETCHK(dalloc(L, wcnt, n));
+        RETCHK(dalloc(L, dsum, n));
         RETCHK(dalloc(L, key, n));
         RETCHK(dalloc(L, rank, n));
         RETCHK(dalloc(L, perm, n));
@@ -1019,7 +1021,7 @@ struct Engine final : EngineBase {
         constexpr int TB = T < LB ? T : LB;
         k_neighbors<D, real, T, TB><<<ntiles, TILE * TB, 0, s>>>(dP, tcase, ctrl, force, x[b][0], x[b][1], x[b][2],
                                                                 cell[b], fstart, geo[b], wx[0], wx[1], wx[2], wstart,
-                                                                wgeo, nbr, ncnt, wnb, wcnt, reinit, st[b], xcum);
+                                                                wgeo, nbr, ncnt, wnb, wcnt, reinit, st[b], xcum, dsum);
     }
 
     // `q` >= 0: at the end of a queue whose last sub-step is q (the scan
@@ -1340,11 +1342,10 @@ struct Engine final : EngineBase {
         RETCHK(push_ctrl());
         k_adv_begin<real><<<(C + 63) / 64, 64, 0, s>>>(dP, ctrl, C);
         HIPCHK(hipGetLastError());
-        // the first step's density re-initialisation, by the same kernel (and
-        // so the same arithmetic) that re-initialises the later steps at the
-        // end of each queue: the lists are rebuilt unchanged from the current
-        // configuration, so how a run is split into calls changes no bit
-        by_lanes([&](auto t) { launch_neighbors<decltype(t)::value>(1, cur, 1); });
+        // the first step's density re-initialisation, from the sums the build
+        // that made the current configuration kept: the values it would have
+        // applied itself, so how a run is split into calls changes no bit
+        k_reinit_start<D, real><<<nblk(ntot), BLOCK, 0, s>>>(dP, tcase, ntiles, ctrl, dsum, st[cur]);
         HIPCHK(hipGetLastError());
         RETCHK(sync_ctrl());
         // queues in batches of at most 64, one host synchronisation per batch
