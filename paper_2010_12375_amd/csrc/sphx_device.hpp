@@ -61,6 +61,9 @@ constexpr int NBATCH = SPHX_BUILD_BATCH;  // candidate rounds loaded ahead per l
 constexpr int XSUB = 4;
 constexpr int CELL_BITS = 28;
 constexpr int32_t CELL_MASK = (1 << CELL_BITS) - 1;
+// list capacity per particle, inner and contact (every case alike)
+template <int D> constexpr int CAP_N = D == 2 ? 48 : 128;
+template <int D> constexpr int CAP_W = D == 2 ? 32 : 96;
 constexpr int VSLOTS = 64;  // slots the density relaxation folds its block maxima into
 #ifndef SPHX_PAIR_WAVES
 #define SPHX_PAIR_WAVES 0
@@ -210,6 +213,9 @@ template <typename T> __device__ __forceinline__ T dmin(T a, T b) { return a < b
 __device__ __forceinline__ float clamp0(float x, float hi) { return __builtin_amdgcn_fmed3f(x, 0.0f, hi); }
 __device__ __forceinline__ double clamp0(double x, double hi) { return dmin(dmax(x, 0.0), hi); }
 
+__device__ __forceinline__ float fma_r(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_r(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // hardware reciprocal square root (about 1 ulp), far inside the FP32 budget
 __device__ __forceinline__ float rsqrt_r(float x) { return __builtin_amdgcn_rsqf(x); }
 __device__ __forceinline__ double rsqrt_r(double x) { return 1.0 / sqrt(x); }
@@ -225,15 +231,49 @@ template <typename real> __device__ __forceinline__ double bits_speed(unsigned l
 template <> __device__ __forceinline__ double bits_speed<float>(unsigned long long b) { return (double)__uint_as_float((uint32_t)b); }
 template <> __device__ __forceinline__ double bits_speed<double>(unsigned long long b) { return __longlong_as_double((long long)b); }
 
-__device__ __forceinline__ float wave_max(float v)
+// Lane exchanges inside rows of 16 lanes by DPP (a modifier of a vector move,
+// no trip through the LDS crossbar as __shfl takes). CTRL: quad_perm
+// [1,0,3,2] and [2,3,0,1] (lane ^ 1, lane ^ 2), row_ror 8 (lane ^ 8),
+// row_shr n, row_bcast 15 and 31.
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_XOR8 = 0x128, DPP_SHR = 0x110, DPP_BCAST15 = 0x142,
+              DPP_BCAST31 = 0x143;
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ float dpp(float v)  // lanes without a source keep their value
 {
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
+    const int x = __float_as_int(v);
+    return __int_as_float(__builtin_amdgcn_update_dpp(x, x, CTRL, ROWS, 0xf, false));
 }
-__device__ __forceinline__ double wave_max(double v)
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ double dpp(double v)
 {
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-    return v;
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false),
+                            __builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false));
+}
+__device__ __forceinline__ float lane63(float v)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+__device__ __forceinline__ double lane63(double v)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                            __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+__device__ __forceinline__ float fmax_r(float a, float b) { return fmaxf(a, b); }
+__device__ __forceinline__ double fmax_r(double a, double b) { return fmax(a, b); }
+
+// Maximum over the wavefront, the same in every lane (a maximum does not
+// depend on the order; NaN gives way to numbers).
+template <typename real>
+__device__ __forceinline__ real wave_max(real v)
+{
+    v = fmax_r(v, dpp<DPP_SHR + 1>(v));
+    v = fmax_r(v, dpp<DPP_SHR + 2>(v));
+    v = fmax_r(v, dpp<DPP_SHR + 4>(v));
+    v = fmax_r(v, dpp<DPP_SHR + 8>(v));
+    v = fmax_r(v, dpp<DPP_BCAST15, 0xa>(v));
+    v = fmax_r(v, dpp<DPP_BCAST31, 0xc>(v));
+    return lane63(v);
 }
 __device__ __forceinline__ double wave_sum(double v)
 {
@@ -241,19 +281,16 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// Sum over the T lanes of a group (groups are aligned inside the wavefront).
-template <int T>
-__device__ __forceinline__ float group_sum(float v)
+// Sum over the T lanes of a group (groups are aligned inside the wavefront),
+// in the order lane ^ T/2, ..., lane ^ 1.
+template <int T, typename real>
+__device__ __forceinline__ real group_sum(real v)
 {
-#pragma unroll
-    for (int o = T / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-template <int T>
-__device__ __forceinline__ double group_sum(double v)
-{
-#pragma unroll
-    for (int o = T / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    static_assert(T <= 16, "groups inside rows of 16 lanes");
+    if constexpr (T >= 16) v += dpp<DPP_XOR8>(v);
+    if constexpr (T >= 8) v += __shfl_xor(v, 4);
+    if constexpr (T >= 4) v += dpp<DPP_XOR2>(v);
+    if constexpr (T >= 2) v += dpp<DPP_XOR1>(v);
     return v;
 }
 
@@ -372,16 +409,18 @@ template <int D, typename real> struct Pair {
 template <int D, typename real, typename G>
 __device__ __forceinline__ Pair<D, real> pair_geo_c(const KP<real>& P, const G& oi, const G& oj, const R4<real>& c)
 {
+#pragma clang fp contract(off)
     Pair<D, real> q;
     real* dx = q.d;
     dx[0] = (oi.x - oj.x) - c.x;
     dx[1] = (oi.y - oj.y) - c.y;
     if constexpr (D == 3) dx[2] = (oi.z - zc(oj)) - c.z;
     else dx[2] = (real)0;
-    real r2 = dx[0] * dx[0] + dx[1] * dx[1] + (D == 3 ? dx[2] * dx[2] : (real)0);
+    real r2 = fma_r(dx[0], dx[0], dx[1] * dx[1]);
+    if constexpr (D == 3) r2 = fma_r(dx[2], dx[2], r2);
     real rinv = rsqrt_r(r2);
     real r = r2 * rinv;
-    real s = (real)1 + P.s_r * r;
+    real s = fma_r(P.s_r, r, (real)1);
     q.dW_r = P.dWr * s * s * s;
     q.dW = q.dW_r * r;
     q.r = r;
@@ -1202,7 +1241,7 @@ __device__ __forceinline__ void close_substep(Ctrl* __restrict__ ctrl, int slot,
 template <typename real>
 __device__ __forceinline__ double slot_max(const unsigned long long* __restrict__ vs)
 {
-    return wave_max(bits_speed<real>(vs[threadIdx.x & 63]));
+    return (double)wave_max((real)bits_speed<real>(vs[threadIdx.x & 63]));
 }
 
 // Start of the advection steps queued by one call (one thread per case); a
@@ -1435,6 +1474,213 @@ __global__ __launch_bounds__(BLOCK) void k_adv_forces(
         Pt, tcase, ctrl_all, gate, geo, wgeo, nbr, ncnt, wnb, wcnt, st, avt, wmot, wvg);
 }
 
+// ---------------------------------------------------------------------
+// Arithmetic of the pressure and density relaxations (S6, S7), shared by the
+// kernels that run them (one launch each, or all sub-steps of a queue in one
+// launch). Multiply-adds are written out and contraction is off, so that every
+// kernel computes the same bits whatever the compiler makes of the code around.
+
+// The particle's own quantities of a relaxation: velocity, rho - rho0 and
+// what follows from them.
+template <typename real> struct Own {
+    real v[3], dev, rho, p;
+};
+template <int D, typename real>
+__device__ __forceinline__ Own<real> own_at(const KP<real>& P, real v0, real v1, real v2, real dev)
+{
+    Own<real> o;
+    o.v[0] = v0;
+    o.v[1] = v1;
+    o.v[2] = D == 3 ? v2 : (real)0;
+    o.dev = dev;
+    o.rho = P.rho0 + dev;
+    o.p = P.c2 * dev;
+    return o;
+}
+// Own quantities of the pressure relaxation: density at the half step.
+template <int D, typename real>
+__device__ __forceinline__ Own<real> own_half(const KP<real>& P, const R4<real>& s, real drho, real half)
+{
+    return own_at<D>(P, s.x, s.y, s.z, fma_r(half, D == 2 ? s.w : drho, D == 2 ? s.z : s.w));
+}
+// ... and of the density relaxation, from the half-step record.
+template <int D, typename real>
+__device__ __forceinline__ Own<real> own_of(const KP<real>& P, const R4<real>& h)
+{
+    return own_at<D>(P, h.x, h.y, h.z, D == 2 ? h.z : h.w);
+}
+
+// n . v
+template <int D, typename real, typename G>
+__device__ __forceinline__ real dot_n(const G& n, const real v[3])
+{
+#pragma clang fp contract(off)
+    real d = fma_r(n.x, v[0], n.y * v[1]);
+    if constexpr (D == 3) d = fma_r(zc(n), v[2], d);
+    return d;
+}
+// (v_i - u) . d
+template <int D, typename real>
+__device__ __forceinline__ real dv_d(const real v[3], const R4<real>& u, const real d[3])
+{
+#pragma clang fp contract(off)
+    real s = fma_r(v[0] - u.x, d[0], (v[1] - u.y) * d[1]);
+    if constexpr (D == 3) s = fma_r(v[2] - u.z, d[2], s);
+    return s;
+}
+// g . r_fw with r_fw = x_w - x_i = -d
+template <int D, typename real>
+__device__ __forceinline__ real g_rfw(const KP<real>& P, const real d[3])
+{
+#pragma clang fp contract(off)
+    real s = fma_r(P.g[0], d[0], P.g[1] * d[1]);
+    if constexpr (D == 3) s = fma_r(P.g[2], d[2], s);
+    return -s;
+}
+template <int D, typename real>
+__device__ __forceinline__ void sub_cd(real acc[3], real cd, const real d[3])
+{
+    acc[0] = fma_r(-cd, d[0], acc[0]);
+    acc[1] = fma_r(-cd, d[1], acc[1]);
+    if constexpr (D == 3) acc[2] = fma_r(-cd, d[2], acc[2]);
+}
+
+// Pressure relaxation, one fluid neighbour (record sj; in 3D its density rate
+// is the w of its frozen offsets, drho_j). mi = 2 m / rho_i.
+template <int D, typename real>
+__device__ __forceinline__ void pressure_fluid(const KP<real>& P, const Own<real>& o, const Pair<D, real>& pq,
+                                               const R4<real>& sj, real drho_j, real half, real mi, real acc[3])
+{
+#pragma clang fp contract(off)
+    const real dev_j = D == 2 ? fma_r(half, sj.w, sj.z) : fma_r(half, drho_j, sj.w);
+    // U_L - U_R = (v_i - v_j) . e_ij = -(v_i - v_j) . d / r
+    const real du = -dv_d<D>(o.v, sj, pq.d) * pq.rinv;
+    const real rho_j = P.rho0 + dev_j;
+    const real qbeta = clamp0((real)0.75 * du, P.quarter_c);  // beta / 4 = min(3 max(du, 0), c) / 4
+    const real ps = fma_r((real)0.5, fma_r(P.c2, dev_j, o.p), qbeta * (o.rho + rho_j) * du);
+    // coef e_ij with coef = 2 m ps W' / (rho_i rho_j), e_ij = -d / r
+    sub_cd<D>(acc, div_r(mi * ps, rho_j) * pq.dW_r, pq.d);
+}
+
+// ... one wall neighbour (normal nw, normal velocity u_w = -n_w . v_w of the
+// wall). wi = 2 V_w / rho_i.
+template <int D, typename real, typename G>
+__device__ __forceinline__ void pressure_wall(const KP<real>& P, const Own<real>& o, const Pair<D, real>& pq,
+                                              const G& nw, real uw, real wi, real acc[3])
+{
+#pragma clang fp contract(off)
+    const real UL = -dot_n<D>(nw, o.v);
+    const real du = (real)2 * (UL - uw);  // U_L - U_R with U_R = -U_L + 2 u_w
+    const real pR = fma_r(o.rho, g_rfw<D>(P, pq.d), o.p);
+    const real rhoR = fma_r(pR, P.inv_c2, P.rho0);
+    const real qbeta = clamp0((real)0.75 * du, P.quarter_c);  // beta / 4
+    const real ps = fma_r((real)0.5, o.p + pR, qbeta * (o.rho + rhoR) * du);
+    sub_cd<D>(acc, wi * ps * pq.dW_r, pq.d);
+}
+
+// The half-step record {v^{n+1}, rho^{n+1/2} - rho0} from the summed pair
+// accelerations, which become the total (with `shear`, plus av).
+template <int D, typename real>
+__device__ __forceinline__ R4<real> pressure_finish(const KP<real>& P, const Own<real>& o, bool shear, const R4<real>& av, real dt,
+                                                    real acc[3])
+{
+#pragma clang fp contract(off)
+    acc[0] += P.g[0];
+    acc[1] += P.g[1];
+    acc[2] += P.g[2];
+    if (shear) {
+        acc[0] += av.x;
+        acc[1] += av.y;
+        acc[2] += av.z;
+    }
+    R4<real> h;
+    h.x = fma_r(dt, acc[0], o.v[0]);
+    h.y = fma_r(dt, acc[1], o.v[1]);
+    if (D == 2) {
+        h.z = o.dev;
+        h.w = 0;
+    } else {
+        h.z = fma_r(dt, acc[2], o.v[2]);
+        h.w = o.dev;
+    }
+    return h;
+}
+
+// Density relaxation, one fluid neighbour (half-step record hj).
+template <int D, typename real>
+__device__ __forceinline__ void density_fluid(const KP<real>& P, const Own<real>& o, const Pair<D, real>& pq,
+                                              const R4<real>& hj, real two_c, real half_m, real& sum)
+{
+#pragma clang fp contract(off)
+    const real dev_j = D == 2 ? hj.z : hj.w;
+    const real rho_j = P.rho0 + dev_j;
+    const real inv_rho_j = div_r((real)1, rho_j);
+    // U* - U_L = (U_R - U_L) / 2 + (p_i - p_j) / (2 rho_bar c) with
+    // rho_bar = (rho_i + rho_j) / 2 and p = c^2 (rho - rho0):
+    // 2 (U* - U_L) = (v_i - v_j) . d / r + 2 c (dev_i - dev_j) / (rho_i + rho_j)
+    // (U_R - U_L = (v_j - v_i) . e_ij = (v_i - v_j) . d / r)
+    const real dus2 = fma_r(dv_d<D>(o.v, hj, pq.d), pq.rinv, div_r(two_c * (o.dev - dev_j), o.rho + rho_j));
+    sum = fma_r(half_m * inv_rho_j * dus2, pq.dW, sum);
+}
+
+// ... one wall neighbour. `moving`: the wall has a velocity, u_w along -n_w.
+template <int D, typename real, typename G>
+__device__ __forceinline__ void density_wall(const KP<real>& P, const Own<real>& o, const Pair<D, real>& pq, const G& nw,
+                                             bool moving, real uw, real& sum)
+{
+#pragma clang fp contract(off)
+    const real UL = -dot_n<D>(nw, o.v);
+    const real pR = fma_r(o.rho, g_rfw<D>(P, pq.d), o.p);
+    const real rhoR = fma_r(pR, P.inv_c2, P.rho0);
+    const real rho_bar = (real)0.5 * (o.rho + rhoR);
+    real us = div_r((o.p - pR) * P.half_inv_c, rho_bar);  // + (U_L + U_R)/2 = u_w below
+    if (moving) us += uw;
+    sum = fma_r(P.vw * (us - UL), pq.dW, sum);
+}
+
+// The end of a sub-step: new record s (velocity v^{n+1}, density at the full
+// step), density rate drho and positions x (both position half-steps; with
+// tv, the transport velocity v + dt at moves them).
+template <int D, typename real>
+__device__ __forceinline__ void density_finish(const KP<real>& P, const Own<real>& o, bool tv, const R4<real>& at, double dtd,
+                                               real sum, R4<real>& s, real& drho, double x[3])
+{
+#pragma clang fp contract(off)
+    drho = (real)2 * o.rho * sum;
+    const double hd = 0.5 * dtd;
+    x[0] = fma_r(hd, (double)s.x, x[0]);
+    x[1] = fma_r(hd, (double)s.y, x[1]);
+    if (D == 3) x[2] = fma_r(hd, (double)s.z, x[2]);
+    x[0] = fma_r(hd, (double)o.v[0], x[0]);
+    x[1] = fma_r(hd, (double)o.v[1], x[1]);
+    if (D == 3) x[2] = fma_r(hd, (double)o.v[2], x[2]);
+    if (tv) {
+        const double d2 = dtd * dtd;
+        x[0] = fma_r(d2, (double)at.x, x[0]);
+        x[1] = fma_r(d2, (double)at.y, x[1]);
+        if (D == 3) x[2] = fma_r(d2, (double)at.z, x[2]);
+    }
+    const real half = (real)0.5 * (real)dtd;
+    s.x = o.v[0];
+    s.y = o.v[1];
+    if (D == 2) {
+        s.z = fma_r(half, drho, o.dev);
+        s.w = drho;
+    } else {
+        s.z = o.v[2];
+        s.w = fma_r(half, drho, o.dev);
+    }
+}
+
+template <int D, typename real>
+__device__ __forceinline__ real speed_of(const real v[3])
+{
+#pragma clang fp contract(off)
+    real q = fma_r(v[0], v[0], v[1] * v[1]);
+    if constexpr (D == 3) q = fma_r(v[2], v[2], q);
+    return sqrt(q);
+}
+
 // The pair kernels below take MOVE = true only for batches with moving
 // walls; the static instantiation compiles none of the wall-velocity code.
 // ---------------------------------------------------------------------
@@ -1500,17 +1746,8 @@ __device__ __forceinline__ void pressure_body(
     real Vw[3] = {0, 0, 0}, omw = 0;
     if (mv) wall_rates(P, ctrl->t + S.tau, Vw, omw);
     const R4<real> si = st[i];
-    real vi[3], dev_i;
-    if (D == 2) {
-        vi[0] = si.x; vi[1] = si.y; vi[2] = 0;
-        dev_i = si.z + half * si.w;
-    } else {
-        vi[0] = si.x; vi[1] = si.y; vi[2] = si.z;
-        dev_i = si.w + half * dr3[i];  // (= geo[i].w)
-    }
-    const real rho_i = P.rho0 + dev_i;
-    const real p_i = P.c2 * dev_i;
-    const real inv_rho_i = (real)1 / rho_i;
+    const Own<real> o = own_half<D>(P, si, D == 3 ? dr3[i] : (real)0, half);  // (dr3[i] = geo[i].w)
+    const real inv_rho_i = (real)1 / o.rho;
     const real mi = P.two_m * inv_rho_i;   // 2 m / rho_i
     const real wi = P.two_vw * inv_rho_i;  // 2 V_w / rho_i
     const G oi = geo[i];
@@ -1518,7 +1755,7 @@ __device__ __forceinline__ void pressure_body(
     struct FluidJ { G o; R4<real> s; };
     struct WallJ { G o; G n; R4<real> k, g; };
     for_pairs<T, BATCH, TL>(
-        nbr, i, ncnt[i], P.maxn, l,
+        nbr, i, ncnt[i], CAP_N<D>, l,
         [&](uint32_t e) {
             uint32_t j = e & NBR_MASK;
             FluidJ r;
@@ -1527,26 +1764,11 @@ __device__ __forceinline__ void pressure_body(
             return r;
         },
         [&](uint32_t e, const FluidJ& r) {
-            Pair<D, real> pq = pair_geo_c<D, real>(P, oi, r.o, coff[e >> NBR_SHIFT]);
-            const R4<real>& sj = r.s;
-            // 3D: the neighbour's density rate is the w of its frozen offsets
-            real dev_j = D == 2 ? sj.z + half * sj.w : sj.w + half * geo_w(r.o);
-            // U_L - U_R = (v_i - v_j) . e_ij = -(v_i - v_j) . d / r
-            real dvd = (vi[0] - sj.x) * pq.d[0] + (vi[1] - sj.y) * pq.d[1] +
-                       (D == 3 ? (vi[2] - sj.z) * pq.d[2] : (real)0);
-            real du = -dvd * pq.rinv;
-            real rho_j = P.rho0 + dev_j;
-            real p_j = P.c2 * dev_j;
-            real qbeta = clamp0((real)0.75 * du, P.quarter_c);  // beta / 4 = min(3 max(du, 0), c) / 4
-            real ps = (real)0.5 * (p_i + p_j) + qbeta * (rho_i + rho_j) * du;
-            // coef e_ij with coef = 2 m ps W' / (rho_i rho_j), e_ij = -d / r
-            real cd = div_r(mi * ps, rho_j) * pq.dW_r;
-            acc[0] -= cd * pq.d[0];
-            acc[1] -= cd * pq.d[1];
-            if (D == 3) acc[2] -= cd * pq.d[2];
+            const Pair<D, real> pq = pair_geo_c<D, real>(P, oi, r.o, coff[e >> NBR_SHIFT]);
+            pressure_fluid<D>(P, o, pq, r.s, geo_w(r.o), half, mi, acc);
         });
     for_pairs<T, BATCH, TL>(
-        wnb, i, wcnt[i], P.maxw, l,
+        wnb, i, wcnt[i], CAP_W<D>, l,
         [&](uint32_t e) {
             uint32_t w = e & NBR_MASK;
             WallJ r;
@@ -1557,52 +1779,24 @@ __device__ __forceinline__ void pressure_body(
             return r;
         },
         [&](uint32_t e, const WallJ& r) {
-            Pair<D, real> pq = pair_geo_c<D, real>(P, oi, r.o, coff[e >> NBR_SHIFT]);
-            const G& nw = r.n;
-            real UL = -(nw.x * vi[0] + nw.y * vi[1] + (D == 3 ? zc(nw) * vi[2] : (real)0));
+            const Pair<D, real> pq = pair_geo_c<D, real>(P, oi, r.o, coff[e >> NBR_SHIFT]);
             real uw = 0;  // u_w = -n_w . v_w, zero for a static wall
             if (mv || gv) {
                 real vw[3] = {0, 0, 0};
                 if (mv) wall_velocity(r.k, Vw, omw, vw);
                 if (gv) add_given(r.g, vw);
-                uw = -(nw.x * vw[0] + nw.y * vw[1] + (D == 3 ? zc(nw) * vw[2] : (real)0));
+                uw = -dot_n<D>(r.n, vw);
             }
-            real du = (real)2 * (UL - uw);  // U_L - U_R with U_R = -U_L + 2 u_w
-            // g . r_fw with r_fw = x_w - x_i = -d
-            real gr = -(P.g[0] * pq.d[0] + P.g[1] * pq.d[1] + (D == 3 ? P.g[2] * pq.d[2] : (real)0));
-            real pR = p_i + rho_i * gr;
-            real rhoR = P.rho0 + pR * P.inv_c2;
-            real qbeta = clamp0((real)0.75 * du, P.quarter_c);  // beta / 4
-            real ps = (real)0.5 * (p_i + pR) + qbeta * (rho_i + rhoR) * du;
-            real cd = wi * ps * pq.dW_r;
-            acc[0] -= cd * pq.d[0];
-            acc[1] -= cd * pq.d[1];
-            if (D == 3) acc[2] -= cd * pq.d[2];
+            pressure_wall<D>(P, o, pq, r.n, uw, wi, acc);
         });
     acc[0] = group_sum<T>(acc[0]);
     acc[1] = group_sum<T>(acc[1]);
     if (D == 3) acc[2] = group_sum<T>(acc[2]);
     if (l != 0) return;
-    acc[0] += P.g[0];
-    acc[1] += P.g[1];
-    acc[2] += P.g[2];
-    if (avt && P.adv_forces) {  // shear force of the advection step
-        const R4<real> a = avt[2 * (size_t)i];
-        acc[0] += a.x;
-        acc[1] += a.y;
-        acc[2] += a.z;
-    }
-    R4<real> o;
-    o.x = vi[0] + dt * acc[0];
-    o.y = vi[1] + dt * acc[1];
-    if (D == 2) {
-        o.z = dev_i;
-        o.w = 0;
-    } else {
-        o.z = vi[2] + dt * acc[2];
-        o.w = dev_i;
-    }
-    hf[i] = o;
+    R4<real> av = {};
+    const bool shear = avt && P.adv_forces;  // shear force of the advection step
+    if (shear) av = avt[2 * (size_t)i];
+    hf[i] = pressure_finish<D>(P, o, shear, av, dt, acc);
     if (acc_out) {
         acc_out[(size_t)i * D + 0] = acc[0];
         acc_out[(size_t)i * D + 1] = acc[1];
@@ -1657,14 +1851,12 @@ __device__ __forceinline__ void density_body(
     Ctrl* ctrl = ctrl_all + P.case_id;
     const SubState S = ctrl->ss[q & 1];
     if (!S.active || ctrl->err) return;
-    __shared__ double smax[BLOCK / 64];
+    __shared__ real smax[BLOCK / 64];
     __shared__ R4<real> coff[64];
     fill_cell_offsets(P, coff);
     __syncthreads();
     using G = typename GeoSel<D, real>::T;
     const double dtd = S.dt;
-    const real dt = (real)dtd;
-    const real half = (real)0.5 * dt;
     const int i = i0 + (int)threadIdx.x / T;
     const int l = threadIdx.x % T;
     // moving walls: velocity rates at the sub-step's end (the level of v^{n+1}),
@@ -1675,13 +1867,7 @@ __device__ __forceinline__ void density_body(
     real speed = 0;
     uint32_t bad = 0;
     if (i < P.fbase + P.nf) {
-        const R4<real> hi_ = hf[i];
-        real vi[3];
-        vi[0] = hi_.x; vi[1] = hi_.y;
-        vi[2] = D == 3 ? hi_.z : (real)0;
-        const real dev_i = D == 2 ? hi_.z : hi_.w;
-        const real rho_i = P.rho0 + dev_i;
-        const real p_i = P.c2 * dev_i;
+        const Own<real> o = own_of<D>(P, hf[i]);
         const real two_c = (real)2 * P.c, half_m = (real)0.5 * P.m;
         const G oi = geo[i];
         // the particle's own state for the final half-steps, loaded ahead of
@@ -1699,7 +1885,7 @@ __device__ __forceinline__ void density_body(
         struct HalfJ { G o; R4<real> h; };
         struct WallJ { G o; G n; R4<real> k, g; };
         for_pairs<T, BATCH, T>(
-            nbr, i, ncnt[i], P.maxn, l,
+            nbr, i, ncnt[i], CAP_N<D>, l,
             [&](uint32_t e) {
                 uint32_t j = e & NBR_MASK;
                 HalfJ r;
@@ -1708,22 +1894,11 @@ __device__ __forceinline__ void density_body(
                 return r;
             },
             [&](uint32_t e, const HalfJ& r) {
-                Pair<D, real> pq = pair_geo_c<D, real>(P, oi, r.o, coff[e >> NBR_SHIFT]);
-                const R4<real>& hj = r.h;
-                real dev_j = D == 2 ? hj.z : hj.w;
-                // U_R - U_L = (v_j - v_i) . e_ij = (v_i - v_j) . d / r
-                real dvd = (vi[0] - hj.x) * pq.d[0] + (vi[1] - hj.y) * pq.d[1] +
-                           (D == 3 ? (vi[2] - hj.z) * pq.d[2] : (real)0);
-                real rho_j = P.rho0 + dev_j;
-                real inv_rho_j = div_r((real)1, rho_j);
-                // U* - U_L = (U_R - U_L) / 2 + (p_i - p_j) / (2 rho_bar c) with
-                // rho_bar = (rho_i + rho_j) / 2 and p = c^2 (rho - rho0):
-                // 2 (U* - U_L) = (v_i - v_j) . d / r + 2 c (dev_i - dev_j) / (rho_i + rho_j)
-                real dus2 = dvd * pq.rinv + div_r(two_c * (dev_i - dev_j), rho_i + rho_j);
-                sum += half_m * inv_rho_j * dus2 * pq.dW;
+                const Pair<D, real> pq = pair_geo_c<D, real>(P, oi, r.o, coff[e >> NBR_SHIFT]);
+                density_fluid<D>(P, o, pq, r.h, two_c, half_m, sum);
             });
         for_pairs<T, BATCH, T>(
-            wnb, i, wcnt[i], P.maxw, l,
+            wnb, i, wcnt[i], CAP_W<D>, l,
             [&](uint32_t e) {
                 uint32_t w = e & NBR_MASK;
                 WallJ r;
@@ -1734,67 +1909,41 @@ __device__ __forceinline__ void density_body(
                 return r;
             },
             [&](uint32_t e, const WallJ& r) {
-                Pair<D, real> pq = pair_geo_c<D, real>(P, oi, r.o, coff[e >> NBR_SHIFT]);
-                const G& nw = r.n;
-                real UL = -(nw.x * vi[0] + nw.y * vi[1] + (D == 3 ? zc(nw) * vi[2] : (real)0));
-                // g . r_fw with r_fw = x_w - x_i = -d
-                real gr = -(P.g[0] * pq.d[0] + P.g[1] * pq.d[1] + (D == 3 ? P.g[2] * pq.d[2] : (real)0));
-                real pR = p_i + rho_i * gr;
-                real rhoR = P.rho0 + pR * P.inv_c2;
-                real rho_bar = (real)0.5 * (rho_i + rhoR);
-                real us = div_r((p_i - pR) * P.half_inv_c, rho_bar);  // + (U_L + U_R)/2 = u_w below
+                const Pair<D, real> pq = pair_geo_c<D, real>(P, oi, r.o, coff[e >> NBR_SHIFT]);
+                real uw = 0;
                 if (mv || gv) {
                     real vw[3] = {0, 0, 0};
                     if (mv) wall_velocity(r.k, Vw, omw, vw);
                     if (gv) add_given(r.g, vw);
-                    us += -(nw.x * vw[0] + nw.y * vw[1] + (D == 3 ? zc(nw) * vw[2] : (real)0));
+                    uw = -dot_n<D>(r.n, vw);
                 }
-                sum += P.vw * (us - UL) * pq.dW;
+                density_wall<D>(P, o, pq, r.n, mv || gv, uw, sum);
             });
         sum = group_sum<T>(sum);
         if (l == 0) {
-            const real drho = (real)2 * rho_i * sum;
             if (!ahead) {
                 so = st[i];
                 xo[0] = x0[i];
                 xo[1] = x1[i];
                 if (D == 3) xo[2] = x2[i];
             }
-            const double hd = 0.5 * dtd;
-            xo[0] = xo[0] + hd * (double)so.x;
-            xo[1] = xo[1] + hd * (double)so.y;
-            if (D == 3) xo[2] = xo[2] + hd * (double)so.z;
-            xo[0] = xo[0] + hd * (double)vi[0];
-            xo[1] = xo[1] + hd * (double)vi[1];
-            if (D == 3) xo[2] = xo[2] + hd * (double)vi[2];
-            if (avt && P.p0 != (real)0) {
-                // positions move with the transport velocity v + dt atv
-                const R4<real> a = avt[2 * (size_t)i + 1];
-                const double d2 = dtd * dtd;
-                xo[0] = xo[0] + d2 * (double)a.x;
-                xo[1] = xo[1] + d2 * (double)a.y;
-                if (D == 3) xo[2] = xo[2] + d2 * (double)a.z;
-            }
+            R4<real> at = {};
+            const bool tv = avt && P.p0 != (real)0;
+            if (tv) at = avt[2 * (size_t)i + 1];
+            real drho;
+            density_finish<D>(P, o, tv, at, dtd, sum, so, drho, xo);
             x0[i] = xo[0];
             x1[i] = xo[1];
-            if (D == 3) x2[i] = xo[2];
-            R4<real> sn;
-            sn.x = vi[0];
-            sn.y = vi[1];
-            if (D == 2) {
-                sn.z = dev_i + half * drho;
-                sn.w = drho;
-            } else {
-                sn.z = vi[2];
-                sn.w = dev_i + half * drho;
+            if (D == 3) {
+                x2[i] = xo[2];
                 dr3[i] = drho;
                 // and in w of the frozen offsets, where the pressure relaxation
                 // gathers it with them (the pair loops here read x, y, z only)
                 reinterpret_cast<real*>(const_cast<G*>(geo))[4 * (size_t)i + 3] = drho;
             }
-            st[i] = sn;
+            st[i] = so;
             if (drho_out) drho_out[i] = drho;
-            speed = sqrt(vi[0] * vi[0] + vi[1] * vi[1] + vi[2] * vi[2]);
+            speed = speed_of<D>(o.v);
             if (drho != drho || speed != speed) bad = ERR_NAN;
         }
     }
@@ -1803,16 +1952,16 @@ __device__ __forceinline__ void density_body(
     // block maximum of |v^{n+1}| into the case's slots of this sub-step,
     // read by the next pressure relaxation or the step end (no cross-block
     // signalling here: a device-wide fence per block would write back L2)
-    double m = wave_max((double)speed);
+    const real m = wave_max(speed);
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     if (lane == 0) smax[wid] = m;
     __syncthreads();
     if (threadIdx.x == 0) {
-        double bm = smax[0];
-        for (int w = 1; w < pair_threads<T>() / 64; ++w) bm = fmax(bm, smax[w]);
+        real bm = smax[0];
+        for (int w = 1; w < pair_threads<T>() / 64; ++w) bm = fmax_r(bm, smax[w]);
         // relaxed, result unused: no wait, no fence; read after the kernel ends
         unsigned long long* vslot = vslot_all + (size_t)P.case_id * 2 * VSLOTS;
-        atomicMax(&vslot[(q & 1) * VSLOTS + (b & (VSLOTS - 1))], speed_bits((real)bm));
+        atomicMax(&vslot[(q & 1) * VSLOTS + (b & (VSLOTS - 1))], speed_bits(bm));
     }
 }
 

@@ -392,8 +392,8 @@ struct Engine final : EngineBase {
 
     int init() override
     {
-        maxn = D == 2 ? 48 : 128;
-        maxw = D == 2 ? 32 : 96;
+        maxn = CAP_N<D>;
+        maxw = CAP_W<D>;
         hP.resize(C);
         pend.assign(C, Pending{});
         wpos_h.assign(C, {});
