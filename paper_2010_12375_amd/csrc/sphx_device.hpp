@@ -1148,6 +1148,314 @@ __global__ __launch_bounds__(TILE * TB) void k_neighbors(
 }
 
 // ---------------------------------------------------------------------
+// S2 in 3D with FP64 records: the same lists as k_neighbors, bit for bit,
+// found in two stages. A block is one tile; each wavefront takes NB_UNIT
+// consecutive particles, which are neighbours in the sorted order: they
+// nearly always lie in two x-adjacent cells, and the cells their 2h reaches
+// cover in a stencil row are one contiguous range (of its fluid particles
+// those in x sub-bins out of everyone's reach are skipped).
+//
+// Sieve: the ranges of the stencil rows, one after the other, fill the lanes
+// of the wavefront with candidates. Full, each lane tests its candidate (its
+// position relative to the first particle, FP32) against one particle of the
+// wavefront after the other, whose coordinates are uniform: r_ij^2 - |x_i|^2
+// as |x_j|^2 - 2 x_i . x_j, three multiply-adds and a compare, with a
+// threshold that lets everything below 2h pass. The ballot gives each hit its
+// place in the particle's list of hits in LDS. Its margin: rounding the
+// coordinates, |x_j|^2, the three multiply-adds and the threshold errs by less
+// than 34 * 2^-24 R^2, R the larger of |x_i| and |x_j|; for a pair within 2h
+// <= L, R^2 <= 2 (|x_i|^2 + L^2), so less than 4.1e-6 (|x_i|^2 + L^2); the
+// sieve allows 1e-5 (|x_i|^2 + L^2).
+//
+// Check: eight lanes per particle go through its hits, densely: the exact
+// predicate, the entry's cell offset, the kernel sum, and the compaction over
+// what the sieve let through too much (the particle itself among it). They
+// write a list's words eight at a time.
+//
+// Bound by vector-ALU issue (3090 instructions a wavefront, half of them in
+// the sieve) and the memory round trips of its ten rounds of checks. 80 k
+// particles: 93 us; k_neighbors, which tests every candidate in FP64 by lanes
+// of its own particle, took 190 us with two lanes a particle, 171 with four,
+// 158 with eight. Half a tile a block and five wavefronts per SIMD: 107 us
+// with whole tiles at four, 98 at six (registers spilled). With FP32 records
+// the test of a candidate is cheap and this split loses: 1.45 ms against 1.13
+// at 2.0 M particles; in 2D, where half of the candidates are neighbours,
+// 412 us against 151 at 1.15 M.
+constexpr int NB_UNIT = 8;                              // particles per wavefront
+constexpr int NB_WAVES = 4;                             // wavefronts per block
+constexpr int NB_BLOCKS = TILE / (NB_UNIT * NB_WAVES);  // blocks per tile
+constexpr int NB_HITS = 152;                            // hits kept per particle between checks (eight blocks fit a CU's LDS)
+
+// p[j] by a 32-bit byte offset (every array of a particle's values is below
+// 4 GB: 2^NBR_SHIFT entries of at most 32 bytes).
+template <typename V>
+__device__ __forceinline__ const V& at32(const V* p, uint32_t j)
+{
+    return *(const V*)((const char*)p + j * (uint32_t)sizeof(V));
+}
+
+template <int T>
+__global__ __launch_bounds__(64 * NB_WAVES) __attribute__((amdgpu_waves_per_eu(5))) void k_neighbors_wave(
+    const KP<double>* __restrict__ Pt, const int32_t* __restrict__ tcase, Ctrl* __restrict__ ctrl_all, int force,
+    const double* __restrict__ x0, const double* __restrict__ x1, const double* __restrict__ x2,
+    const int32_t* __restrict__ cell, const int32_t* __restrict__ fstart,
+    const GeoSel<3, double>::T* __restrict__ geo, const double* __restrict__ wx0,
+    const double* __restrict__ wx1, const double* __restrict__ wx2, const int32_t* __restrict__ wstart,
+    const GeoSel<3, double>::T* __restrict__ wgeo, uint32_t* __restrict__ nbr, int32_t* __restrict__ ncnt,
+    uint32_t* __restrict__ wnb, int32_t* __restrict__ wcnt, int reinit, R4<double>* __restrict__ st,
+    const uint32_t* __restrict__ xcum, double* __restrict__ dsum)
+{
+    using G = GeoSel<3, double>::T;
+    constexpr int ROWS = 9;
+    struct Axis { double half, period; };  // minimum image; half is infinite on an axis that is not periodic
+    __shared__ uint32_t hits[NB_WAVES][NB_UNIT][NB_HITS];
+    __shared__ float4 unit[NB_WAVES][NB_UNIT];  // -2 x_i and the threshold
+    __shared__ __align__(16) Axis axis[3];
+    const int b = xcd_block(blockIdx.x, gridDim.x);
+    const KP<double>& P = Pt[tcase[b / NB_BLOCKS]];
+    Ctrl* ctrl = ctrl_all + P.case_id;
+    if (!full_update(ctrl, force)) return;
+    if (threadIdx.x < 3) {
+        const int k = threadIdx.x;
+        axis[k].half = P.periodic[k] ? P.half_period[k] : __longlong_as_double(0x7ff0000000000000ll);
+        axis[k].period = P.period[k];
+    }
+    __syncthreads();
+    if (ctrl->err) return;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int p = lane >> 3, c8 = lane & 7;  // the lane's particle of the unit, and its place in the check
+    const int i = (b * NB_WAVES + wv) * NB_UNIT + p;
+    const int fend = P.fbase + P.nf, wend = P.wbase + P.nw;
+    const bool used = i < fend;
+    if (!__ballot(used)) return;
+    const double xi[3] = {x0[i], x1[i], x2[i]};
+    const G oi = geo[i];
+    const float Lm = (float)dmax(P.L[0], dmax(P.L[1], P.L[2]));
+    const double rc2 = P.rc2;
+    const float rc2f = (float)rc2;
+    const int kw = used ? cell[i] : 0;
+    const int kc = kw & CELL_MASK;
+    const int sb = (int)((uint32_t)kw >> CELL_BITS);
+    int nfl = 0, nwl = 0;  // entries of the lane's particle, inner and contact
+    bool over = false;
+    double sigma = 0.0;
+    auto sync_lds = []() __attribute__((always_inline)) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    auto lane_i = [](int v, int k) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(v, k); };
+    auto lane_d = [](double v, int k) __attribute__((always_inline)) {
+        return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), k),
+                                __builtin_amdgcn_readlane(__double2loint(v), k));
+    };
+    // pair_r2 with the axes from LDS
+    auto exact_r2 = [&](const double* xj) __attribute__((always_inline)) {
+#pragma clang fp contract(off)
+        double t[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const Axis a = axis[k];
+            const double u = xi[k] - xj[k];
+            t[k] = u > a.half ? u - a.period : (u < -a.half ? u + a.period : u);
+        }
+        return t[0] * t[0] + t[1] * t[1] + t[2] * t[2];
+    };
+
+    for (unsigned long long todo = __ballot(used && c8 == 0); todo;) {
+        // The unit's next group of particles: two x-adjacent cells at most;
+        // at the ends of a row of cells, where the stencil is cut or wraps,
+        // one cell.
+        const int f = __ffsll((long long)todo) - 1;
+        const int kf = lane_i(kc, f);
+        int cc[3];
+        cell_coords(P, kf - P.cbase, cc);
+        const bool edge = cc[0] < 1 || cc[0] + 1 >= P.n[0], pair = !edge && cc[0] + 2 < P.n[0];
+        const bool in_group = kc == kf || (pair && kc == kf + 1);
+        const unsigned long long group = __ballot(in_group) & todo;
+        todo &= ~group;
+        const int e = 63 - __clzll((long long)group);
+        const int wide = lane_i(kc, e) - kf;  // 1 if it lies in two cells
+        const int sb_lo = lane_i(sb, f) - P.xsub_margin, sb_hi = lane_i(sb, e) + P.xsub_margin;
+        const bool mine = (group >> (8 * p)) & 1ull;
+        const uint32_t dcx = mine ? (uint32_t)(kc - kf) : 0u;
+        // the particles' coordinates, relative to the group's first; a
+        // threshold nothing is below for those not in the group
+        const double xr[3] = {lane_d(xi[0], f), lane_d(xi[1], f), lane_d(xi[2], f)};
+        {
+            const float a0 = (float)(xi[0] - xr[0]), a1 = (float)(xi[1] - xr[1]),
+                        a2 = (float)(xi[2] - xr[2]);
+            const float nn = a0 * a0 + a1 * a1 + a2 * a2;
+            const float t = mine ? rc2f + (1e-5f * (Lm * Lm + nn) - nn) : -__builtin_inff();
+            if (c8 == 0) unit[wv][p] = float4{-2.f * a0, -2.f * a1, -2.f * a2, t};
+            sync_lds();
+        }
+#pragma unroll 1
+        for (int body = 0; body < 2; ++body) {  // fluid, wall
+            if (body && P.nw == 0) break;
+            const int32_t* cst = body ? wstart : fstart;
+            const double* bx0 = body ? wx0 : x0;
+            const double* bx1 = body ? wx1 : x1;
+            const double* bx2 = body ? wx2 : x2;
+            const G* csrc = body ? wgeo : geo;
+            const int lim = body ? wend : fend, mx = body ? CAP_W<3> : CAP_N<3>;
+            uint32_t* out = (body ? wnb : nbr) + ell_base<T>(i, mx);
+            const uint32_t safe = (uint32_t)(body ? P.wbase : P.fbase);  // an index that can be loaded
+            int nout = body ? nwl : nfl;
+
+            // The candidate ranges of the group, one per lane: the rows of
+            // the stencil (edge: its cells); b1..b3 are the starts of the
+            // cells after the range's first; tag holds the code of the row
+            // (its first cell) and, above bit 8, the image.
+            int j0 = 0, j1 = 0, b1 = 0x7fffffff, b2 = 0x7fffffff, b3 = 0x7fffffff, tag = 0;
+            if (lane < (edge ? 3 * ROWS : ROWS)) {
+                const int r = edge ? lane / 3 : lane;
+                const int dy = r % 3 - 1, dz = r / 3 - 1, dx = edge ? lane % 3 - 1 : 0;
+                int c[3] = {cc[0] + dx, cc[1] + dy, cc[2] + dz};
+                bool ok = true;
+                tag = ((dy + 1) << 2) | ((dz + 1) << 4) | (edge ? dx + 1 : 0);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const bool lo = c[k] < 0, hi = c[k] >= P.n[k];
+                    ok = ok && (P.periodic[k] || !(lo || hi));
+                    tag |= (lo ? 1 : hi ? 2 : 0) << (8 + 2 * k);
+                    c[k] += lo ? P.n[k] : hi ? -P.n[k] : 0;
+                }
+                if (ok) {
+                    const int ca = P.cbase + P.n[0] * cell_row(P, c[1], c[2]) + c[0];
+                    if (edge) {
+                        j0 = cst[ca];
+                        j1 = cst[ca + 1];
+                    } else {
+                        const int cb = ca + wide;
+                        j0 = cst[ca - 1];
+                        b1 = cst[ca];
+                        b2 = cst[ca + 1];
+                        j1 = cst[cb + 2];
+                        if (wide) b3 = cst[ca + 2];
+                        if (!body) {
+                            // (the counts of a cell that has emptied are
+                            // stale: the clamps make them 0)
+                            j0 = min(j0 + xsub_below(xcum[ca - 1], sb_lo), b1);
+                            j1 = max(j1 - xsub_above(xcum[cb + 1], sb_hi), wide ? b3 : b2);
+                        }
+                    }
+                    j0 = min(j0, lim);
+                    j1 = min(j1, lim);
+                }
+            }
+            unsigned long long rows = __ballot(j1 > j0);
+            if (!rows) continue;
+            const bool shifted = __ballot((tag >> 8) != 0 && j1 > j0);
+
+            int cnt[NB_UNIT] = {};
+            int fill = 0, img = 0;
+            uint32_t ent = safe;
+            int r = 0, ja = 0, je = 0;
+            bool more = true;
+            do {
+                // fill the lanes
+                do {
+                    if (ja == je) {
+                        if (!rows) {
+                            more = false;
+                            break;
+                        }
+                        r = __ffsll((long long)rows) - 1;
+                        rows &= rows - 1;
+                        ja = lane_i(j0, r);
+                        je = lane_i(j1, r);
+                    }
+                    const int take = min(je - ja, 64 - fill);
+                    const int j = ja + (lane - fill);
+                    const int rt = lane_i(tag, r);
+                    const uint32_t code = (uint32_t)(rt & 63) + (uint32_t)(j >= lane_i(b1, r)) +
+                                          (uint32_t)(j >= lane_i(b2, r)) + (uint32_t)(j >= lane_i(b3, r));
+                    const bool here = (unsigned)(lane - fill) < (unsigned)take;
+                    ent = here ? (uint32_t)j | (code << NBR_SHIFT) : ent;
+                    img = here ? rt >> 8 : img;
+                    fill += take;
+                    ja += take;
+                } while (fill < 64);
+                int most = 0;
+                if (fill) {
+                    const uint32_t j = ent & NBR_MASK;
+                    double d0 = at32(bx0, j) - xr[0], d1 = at32(bx1, j) - xr[1], d2 = at32(bx2, j) - xr[2];
+                    if (shifted) {
+                        auto image = [&](int k, double d) __attribute__((always_inline)) {
+                            const int m = (img >> (2 * k)) & 3;
+                            return m == 1 ? d - axis[k].period : m == 2 ? d + axis[k].period : d;
+                        };
+                        d0 = image(0, d0);
+                        d1 = image(1, d1);
+                        d2 = image(2, d2);
+                    }
+                    float a0 = (float)d0, a1 = (float)d1, a2 = (float)d2;
+                    float s2 = a0 * a0 + a1 * a1 + a2 * a2;
+                    if (lane >= fill) {  // no candidate: never a hit, whatever the coordinates
+                        a0 = a1 = a2 = 0.f;
+                        s2 = 3e38f;
+                    }
+#pragma unroll
+                    for (int q = 0; q < NB_UNIT; ++q) {
+                        const float4 u = unit[wv][q];
+                        const bool hit = fma_r(u.z, a2, fma_r(u.y, a1, fma_r(u.x, a0, s2))) < u.w;
+                        const unsigned long long m = __ballot(hit);
+                        if (hit)
+                            hits[wv][q][__builtin_amdgcn_mbcnt_hi(
+                                (unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, (unsigned)cnt[q]))] = ent;
+                        cnt[q] += __popcll(m);
+                        most = max(most, cnt[q]);
+                    }
+                    fill = 0;
+                }
+                if (more && most <= NB_HITS - 64) continue;
+
+                // the exact check of the hits found so far
+                sync_lds();
+                int n = 0, nmax = 0;
+#pragma unroll
+                for (int q = 0; q < NB_UNIT; ++q) {
+                    n = p == q ? cnt[q] : n;
+                    nmax = max(nmax, cnt[q]);
+                    cnt[q] = 0;
+                }
+                for (int k = c8; k - c8 < nmax; k += 8) {
+                    bool in = k < n;
+                    const uint32_t hit = in ? hits[wv][p][k] - (dcx << NBR_SHIFT) : safe;
+                    const uint32_t j = hit & NBR_MASK, code = hit >> NBR_SHIFT;
+                    // of the group's range, the three cells around the
+                    // particle's own, without itself
+                    in = in && (code & 3u) != 3u && (body || (int)j != i);
+                    const G oj = at32(csrc, j);
+                    const double xj[3] = {at32(bx0, j), at32(bx1, j), at32(bx2, j)};
+                    in = in && exact_r2(xj) < rc2;
+                    const unsigned ok = (unsigned)(__ballot(in) >> (8 * p)) & 0xffu;
+                    if (in) {
+                        const int slot = nout + __popc(ok & ((1u << c8) - 1u));
+                        if (slot < mx) out[ell_off<T>((unsigned)slot)] = hit;
+                        else over = true;
+                        sigma += (double)kernel_W(P, pair_geo<3, double>(P, oi, oj, code).r);
+                    }
+                    nout += __popc(ok);
+                }
+                sync_lds();
+            } while (more);
+            if (body) nwl = nout;
+            else nfl = nout;
+        }
+    }
+    sigma = group_sum<8>(sigma) + (double)P.Wc;  // + W(0), the particle itself
+    if (over) atomicOr(&ctrl->err, ERR_NBR_OVERFLOW);
+    if (!used || c8 != 0) return;
+    ncnt[i] = min(nfl, CAP_N<3>);
+    wcnt[i] = min(nwl, CAP_W<3>);
+    const double dev_sum = summed_dev(P, sigma);
+    dsum[i] = dev_sum;
+    if (reinit && ctrl->ss[0].active && !ctrl->midstep) reinit_density<3>(P, dev_sum, st + i);
+}
+
+// ---------------------------------------------------------------------
 // S5: the dual-criteria clock (Eqs. dt-advection, dt-relax).
 
 // Sub-step 0 of a new advection step (one thread): dt_ad from |v|max floored
