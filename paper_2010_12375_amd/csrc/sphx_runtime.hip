@@ -1388,6 +1388,25 @@ struct Engine final : EngineBase {
     int get_field(int c, int which, double* out) override { return get_field_impl(c, which, out, false); }
     int get_field_device(int c, int which, double* out) override { return get_field_impl(c, which, out, true); }
 
+    // Whether `out` is aligned memory of this GPU that holds n doubles, which
+    // a kernel can write itself. Everything else goes through outbuf and the
+    // runtime's copy, which checks it.
+    bool kernel_can_write(const double* out, size_t n) const
+    {
+        hipPointerAttribute_t a;
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        if ((uintptr_t)out % alignof(double) == 0 && hipPointerGetAttributes(&a, out) == hipSuccess &&
+            a.type == hipMemoryTypeDevice && a.device == ctx->device &&
+            hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)out) == hipSuccess)
+            return (size_t)((const char*)out - (const char*)base) + n * sizeof(double) <= size;
+        (void)hipGetLastError();
+        return false;
+    }
+
+    // A field read to device memory is written there by the kernel that
+    // restores the order; the copy behind it was a second launch (64 cases
+    // of 18 k particles, ten steps and 128 reads: 10.19 -> 9.78 ms).
     int get_field_impl(int c, int which, double* out, bool device)
     {
         RETCHK(check_case(c));
@@ -1395,12 +1414,14 @@ struct Engine final : EngineBase {
         RETCHK(ensure_layout());
         const KP<real>& P = hP[c];
         if (P.nf == 0) return SPHX_OK;
+        const size_t cnt_out = (which <= 1 ? (size_t)D : 1) * P.nf;
+        const bool direct = device && kernel_can_write(out, cnt_out);
         k_unsort_field<D, real><<<nblk(P.nf), BLOCK, 0, s>>>(dP, c, which, id[cur], x[cur][0], x[cur][1], x[cur][2],
-                                                              st[cur], dr3[cur], outbuf);
+                                                              st[cur], dr3[cur], direct ? out : outbuf);
         HIPCHK(hipGetLastError());
-        size_t cnt_out = (which <= 1 ? (size_t)D : 1) * P.nf;
-        HIPCHK(hipMemcpyAsync(out, outbuf, sizeof(double) * cnt_out,
-                              device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
+        if (!direct)
+            HIPCHK(hipMemcpyAsync(out, outbuf, sizeof(double) * cnt_out,
+                                  device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         return SPHX_OK;
     }
