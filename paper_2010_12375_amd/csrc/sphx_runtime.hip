@@ -247,7 +247,7 @@ struct Engine final : EngineBase {
         free_list(gn.fixed);
         free_list(gn.nodes);
         free_list(gn.edges);
-        for (void* p : {(void*)lb_status, (void*)lb_ticket, (void*)lb_fault, (void*)lb_epoch})
+        for (void* p : {(void*)lb_status, (void*)lb_ticket, (void*)lb_epoch})
             if (p) (void)hipFree(p);
         for (void* p : {(void*)ctrl, (void*)cnt, (void*)fstart, (void*)xcum, (void*)bsum, (void*)wstart, (void*)diag_out,
                         (void*)dP, (void*)vslot, (void*)stage})
@@ -408,10 +408,13 @@ struct Engine final : EngineBase {
         ncell = cbase;
         nsub_q = ctx->prm[0].nsub_queue > 0 ? ctx->prm[0].nsub_queue : 5;
         if (nsub_q > 64) nsub_q = 64;
-        HIPCHK(hipMalloc((void**)&ctrl, sizeof(Ctrl) * C));
-        HIPCHK(hipHostMalloc((void**)&hctrl, sizeof(Ctrl) * C, hipHostMallocDefault));
-        std::memset(hctrl, 0, sizeof(Ctrl) * C);
-        HIPCHK(hipMemcpyAsync(ctrl, hctrl, sizeof(Ctrl) * C, hipMemcpyHostToDevice, s));
+        // the scan's fault word follows the control blocks, so that one copy
+        // into the pinned mirror brings both
+        HIPCHK(hipMalloc((void**)&ctrl, sizeof(Ctrl) * (C + 1)));
+        lb_fault = (int32_t*)(ctrl + C);
+        HIPCHK(hipHostMalloc((void**)&hctrl, sizeof(Ctrl) * (C + 1), hipHostMallocDefault));
+        std::memset(hctrl, 0, sizeof(Ctrl) * (C + 1));
+        HIPCHK(hipMemcpyAsync(ctrl, hctrl, sizeof(Ctrl) * (C + 1), hipMemcpyHostToDevice, s));
         HIPCHK(hipMalloc((void**)&dP, sizeof(KP<real>) * C));
         HIPCHK(hipMalloc((void**)&vslot, sizeof(unsigned long long) * 2 * VSLOTS * C));
         HIPCHK(hipMemsetAsync(vslot, 0, sizeof(unsigned long long) * 2 * VSLOTS * C, s));
@@ -422,11 +425,9 @@ struct Engine final : EngineBase {
         HIPCHK(hipMalloc((void**)&bsum, sizeof(int32_t) * ((size_t)nblk_scan() + 1)));
         HIPCHK(hipMalloc((void**)&lb_status, sizeof(unsigned long long) * (size_t)nblk_lb()));
         HIPCHK(hipMalloc((void**)&lb_ticket, sizeof(int32_t)));
-        HIPCHK(hipMalloc((void**)&lb_fault, sizeof(int32_t)));
         HIPCHK(hipMalloc((void**)&lb_epoch, sizeof(uint32_t)));
         HIPCHK(hipMemsetAsync(lb_status, 0, sizeof(unsigned long long) * (size_t)nblk_lb(), s));
         HIPCHK(hipMemsetAsync(lb_ticket, 0, sizeof(int32_t), s));
-        HIPCHK(hipMemsetAsync(lb_fault, 0, sizeof(int32_t), s));
         {
             const uint32_t one = 1u;  // status words of epoch 0 (zeroed) read as empty
             HIPCHK(hipMemcpyAsync(lb_epoch, &one, sizeof(uint32_t), hipMemcpyHostToDevice, s));
@@ -513,10 +514,10 @@ struct Engine final : EngineBase {
 
     int sync_ctrl()
     {
-        int32_t fault = 0;
-        HIPCHK(hipMemcpyAsync(hctrl, ctrl, sizeof(Ctrl) * C, hipMemcpyDeviceToHost, s));
-        HIPCHK(hipMemcpyAsync(&fault, lb_fault, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        HIPCHK(hipMemcpyAsync(hctrl, ctrl, sizeof(Ctrl) * C + sizeof(int32_t), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
+        int32_t fault;
+        std::memcpy(&fault, hctrl + C, sizeof(fault));
         if (fault) return ctx->fail(SPHX_EHIP, "cell-count scan: look-back wait exceeded its bound");
         bool fold = false;
         for (int c = 0; c < C; ++c)
@@ -1347,6 +1348,10 @@ struct Engine final : EngineBase {
             sub0[c] = hctrl[c].nsub_total;
             hctrl[c].t_stop = t_stop;
             hctrl[c].steps_target = hctrl[c].steps_done + steps[c];
+            // whether k_adv_begin will open a step (its own test): the first
+            // batch of queues is launched without waiting for it
+            if (!hctrl[c].midstep)
+                hctrl[c].ss[0].active = hctrl[c].err == 0 && hctrl[c].t < t_stop && hctrl[c].steps_done < hctrl[c].steps_target;
         }
         RETCHK(push_ctrl());
         k_adv_begin<real><<<(C + 63) / 64, 64, 0, s>>>(dP, ctrl, C);
@@ -1356,9 +1361,14 @@ struct Engine final : EngineBase {
         // applied itself, so how a run is split into calls changes no bit
         k_reinit_start<D, real><<<nblk(ntot), BLOCK, 0, s>>>(dP, tcase, ntiles, ctrl, dsum, st[cur]);
         HIPCHK(hipGetLastError());
-        RETCHK(sync_ctrl());
         // queues in batches of at most 64, one host synchronisation per batch
-        for (long long need = queues_needed(); need > 0; need = queues_needed()) {
+        // and one before the first: the device has no idle gap in front of
+        // its queues (with another one after k_adv_begin, and the fault word
+        // copied by itself into pageable memory, eight steps of a 9 k
+        // cavity took 990 us, without 898)
+        long long need = queues_needed();
+        if (need <= 0) RETCHK(sync_ctrl());
+        for (; need > 0; need = queues_needed()) {
             long long batch = std::min<long long>(need, 64);
             long long q = 0;
             for (; q + steps_per_graph <= batch; q += steps_per_graph) {
