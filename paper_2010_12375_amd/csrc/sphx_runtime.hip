@@ -763,25 +763,50 @@ struct Engine final : EngineBase {
         return load_case(c, n, pos, vel, rho, drho, device);
     }
 
+    // Whether p is aligned memory of this GPU that holds n doubles, which a
+    // kernel can read or write itself. Everything else goes through a buffer
+    // of the context and the runtime's copy, which checks it.
+    bool kernel_can_reach(const double* p, size_t n) const
+    {
+        hipPointerAttribute_t a;
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        if ((uintptr_t)p % alignof(double) == 0 && hipPointerGetAttributes(&a, p) == hipSuccess &&
+            a.type == hipMemoryTypeDevice && a.device == ctx->device &&
+            hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) == hipSuccess)
+            return (size_t)((const char*)p - (const char*)base) + n * sizeof(double) <= size;
+        (void)hipGetLastError();
+        return false;
+    }
+
     // Load case c's fluid (n particles, original order) into its slots of the
     // current set; reset its clock and counters and take its |v|max.
     int load_case(int c, int64_t n, const double* pos, const double* vel, const double* rho, const double* drho,
                   bool device = false)
     {
-        size_t nn = (size_t)n;
-        RETCHK(ensure_stage(nn * (2 * D + 2)));
-        double* dpos = stage;
-        double* dvel = stage + nn * D;
-        double* drh = stage + nn * 2 * D;
-        double* ddr = drh + nn;
-        const hipMemcpyKind kind = device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
+        const size_t nn = (size_t)n;
         if (n > 0) {
-            HIPCHK(hipMemcpyAsync(dpos, pos, nn * D * sizeof(double), kind, s));
-            if (vel) HIPCHK(hipMemcpyAsync(dvel, vel, nn * D * sizeof(double), kind, s));
-            if (rho) HIPCHK(hipMemcpyAsync(drh, rho, nn * sizeof(double), kind, s));
-            if (drho) HIPCHK(hipMemcpyAsync(ddr, drho, nn * sizeof(double), kind, s));
-            k_load_fluid<D, real><<<nblk(n), BLOCK, 0, s>>>(dP, c, dpos, vel ? dvel : nullptr, rho ? drh : nullptr,
-                                                             drho ? ddr : nullptr, x[cur][0], x[cur][1], x[cur][2],
+            // arrays on this GPU are read where they are (32 windowed cases
+            // set and run for three windows: 11.25 -> 9.2 ms, the staging copies
+            // being four launches a case)
+            const bool direct = device && kernel_can_reach(pos, nn * D) && (!vel || kernel_can_reach(vel, nn * D)) &&
+                                (!rho || kernel_can_reach(rho, nn)) && (!drho || kernel_can_reach(drho, nn));
+            if (!direct) {
+                RETCHK(ensure_stage(nn * (2 * D + 2)));
+                double* to = stage;
+                const hipMemcpyKind kind = device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
+                auto staged = [&](const double*& a, size_t cnt) {
+                    const hipError_t e = a ? hipMemcpyAsync(to, a, cnt * sizeof(double), kind, s) : hipSuccess;
+                    if (a) a = to;
+                    to += cnt;
+                    return e;
+                };
+                HIPCHK(staged(pos, nn * D));
+                HIPCHK(staged(vel, nn * D));
+                HIPCHK(staged(rho, nn));
+                HIPCHK(staged(drho, nn));
+            }
+            k_load_fluid<D, real><<<nblk(n), BLOCK, 0, s>>>(dP, c, pos, vel, rho, drho, x[cur][0], x[cur][1], x[cur][2],
                                                              st[cur], dr3[cur], id[cur], cell[cur]);
             HIPCHK(hipGetLastError());
         }
@@ -1398,22 +1423,6 @@ struct Engine final : EngineBase {
     int get_field(int c, int which, double* out) override { return get_field_impl(c, which, out, false); }
     int get_field_device(int c, int which, double* out) override { return get_field_impl(c, which, out, true); }
 
-    // Whether `out` is aligned memory of this GPU that holds n doubles, which
-    // a kernel can write itself. Everything else goes through outbuf and the
-    // runtime's copy, which checks it.
-    bool kernel_can_write(const double* out, size_t n) const
-    {
-        hipPointerAttribute_t a;
-        hipDeviceptr_t base = nullptr;
-        size_t size = 0;
-        if ((uintptr_t)out % alignof(double) == 0 && hipPointerGetAttributes(&a, out) == hipSuccess &&
-            a.type == hipMemoryTypeDevice && a.device == ctx->device &&
-            hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)out) == hipSuccess)
-            return (size_t)((const char*)out - (const char*)base) + n * sizeof(double) <= size;
-        (void)hipGetLastError();
-        return false;
-    }
-
     // A field read to device memory is written there by the kernel that
     // restores the order; the copy behind it was a second launch (64 cases
     // of 18 k particles, ten steps and 128 reads: 10.19 -> 9.78 ms).
@@ -1425,7 +1434,7 @@ struct Engine final : EngineBase {
         const KP<real>& P = hP[c];
         if (P.nf == 0) return SPHX_OK;
         const size_t cnt_out = (which <= 1 ? (size_t)D : 1) * P.nf;
-        const bool direct = device && kernel_can_write(out, cnt_out);
+        const bool direct = device && kernel_can_reach(out, cnt_out);
         k_unsort_field<D, real><<<nblk(P.nf), BLOCK, 0, s>>>(dP, c, which, id[cur], x[cur][0], x[cur][1], x[cur][2],
                                                               st[cur], dr3[cur], direct ? out : outbuf);
         HIPCHK(hipGetLastError());
