@@ -945,7 +945,7 @@ template <int B> struct BodyTag { static constexpr int value = B; };
 // around its cell in the fluid and wall cell lists and keep j != i with
 // r^2 < (2h)^2, the predicate evaluated exactly as stated on the FP64
 // positions. Entries keep the cell offset so that the pair geometry can be
-// rebuilt from cell offsets.
+// rebuilt from cell offsets. (3D with FP64 records: k_neighbors_wave.)
 //
 // TB lanes share one particle; a block is one tile. The three x-adjacent
 // cells of a stencil row are one contiguous range of the sorted order; of

@@ -787,7 +787,7 @@ struct Engine final : EngineBase {
         const size_t nn = (size_t)n;
         if (n > 0) {
             // arrays on this GPU are read where they are (32 windowed cases
-            // set and run for three windows: 11.25 -> 9.2 ms, the staging copies
+            // set and run for four windows: 11.25 -> 9.2 ms, the staging copies
             // being four launches a case)
             const bool direct = device && kernel_can_reach(pos, nn * D) && (!vel || kernel_can_reach(vel, nn * D)) &&
                                 (!rho || kernel_can_reach(rho, nn)) && (!drho || kernel_can_reach(drho, nn));
