@@ -216,9 +216,22 @@ __device__ __forceinline__ double clamp0(double x, double hi) { return dmin(dmax
 __device__ __forceinline__ float fma_r(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_r(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-// hardware reciprocal square root (about 1 ulp), far inside the FP32 budget
+// Reciprocal square root. FP32: the hardware's (about 1 ulp), far inside the
+// FP32 budget. FP64: the hardware's estimate y (2^-24) and one third-order
+// Newton step, y (1 + e/2 + 3/8 e^2) with e = 1 - x y^2: ten instructions
+// where a square root and a division, each rounded correctly, take 27 in a
+// chain (10 steps of 800 particles 988 -> 938 us, 3 steps of 80 k in 3D 1440 ->
+// 1382). Largest and rms error 1.25 and 0.48 of 2^-53 against 1.49 and 0.60
+// (4 M values in each of 1e-300..1e-200, 1e-12..1e4, 1e200..1e300). Where e
+// is NaN (x zero, infinite, NaN or negative) the estimate is the result.
 __device__ __forceinline__ float rsqrt_r(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double rsqrt_r(double x) { return 1.0 / sqrt(x); }
+__device__ __forceinline__ double rsqrt_r(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = __builtin_fma(-(x * y), y, 1.0);
+    const double z = __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+    return e == e ? z : y;
+}
 // Quotients inside the pair loops: in FP32 a times the hardware reciprocal
 // of b (within about 1 ulp of the reciprocal; two instructions instead of
 // the correctly rounded division's eleven), in FP64 the division itself.
