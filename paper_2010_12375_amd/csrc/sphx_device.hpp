@@ -1185,11 +1185,11 @@ __global__ __launch_bounds__(TILE * TB) void k_neighbors(
 // what the sieve let through too much (the particle itself among it). They
 // write a list's words eight at a time.
 //
-// Bound by vector-ALU issue (3090 instructions a wavefront, half of them in
-// the sieve) and the memory round trips of its ten rounds of checks. 80 k
-// particles: 93 us; k_neighbors, which tests every candidate in FP64 by lanes
+// Bound by vector-ALU issue (3090 instructions a wavefront, about 1150 each in
+// the sieve and in the checks) and the round trips of its ten checks. 80 k
+// particles: 88 us; k_neighbors, which tests every candidate in FP64 by lanes
 // of its own particle, took 190 us with two lanes a particle, 171 with four,
-// 158 with eight. Half a tile a block and five wavefronts per SIMD: 107 us
+// 158 with eight. Half a tile a block and five wavefronts per SIMD; 107 us
 // with whole tiles at four, 98 at six (registers spilled). With FP32 records
 // the test of a candidate is cheap and this split loses: 1.45 ms against 1.13
 // at 2.0 M particles; in 2D, where half of the candidates are neighbours,

@@ -1042,7 +1042,7 @@ struct Engine final : EngineBase {
     template <int T>
     void launch_neighbors(int force, int b, int reinit = 0)
     {
-        // 3D with FP64 records: the wavefront-wide sieve (190 -> 93 us at 80 k
+        // 3D with FP64 records: the wavefront-wide sieve (190 -> 88 us at 80 k
         // particles; slower than k_neighbors in 2D and with FP32 records)
         if constexpr (D == 3 && sizeof(real) == 8) {
             k_neighbors_wave<T><<<ntiles * NB_BLOCKS, 64 * NB_WAVES, 0, s>>>(
