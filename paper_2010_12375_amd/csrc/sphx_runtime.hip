@@ -1797,8 +1797,6 @@ struct Engine final : EngineBase {
                     nullptr);
             });
         }));
-        // the list build is idempotent on the current set
-        RETCHK(time_launches(reps, &ms[2], [&] { launch_neighbors<T>(1, a); }));
         RETCHK(time_launches(reps, &ms[3], [&] {
             k_reinit<D, real, T><<<nb, pair_threads<T>(), 0, s>>>(dP, tcase, ctrl, 0, geo[a], wgeo, nbr, ncnt, wnb, wcnt, st[a]);
         }));
@@ -1806,13 +1804,21 @@ struct Engine final : EngineBase {
     }
 
     // Per-launch device time of the hot kernels on the current state of
-    // every case (each case one sub-step of its own dt_ac); the state and the
-    // clocks are restored afterwards.
+    // every case (each case one sub-step of its own dt_ac); the state, the
+    // lists and the clocks are as before afterwards, also where a launch
+    // fails. The list build is timed first, before a density relaxation has
+    // moved a particle, and with the error bits as they are: it writes the
+    // lists and sums that are there already (a case in error is left out).
     int profile(int32_t reps, double* ms) override
     {
         if (!configured) return ctx->fail(SPHX_ESTATE, "no neighbour configuration");
         if (reps < 1 || !ms) return ctx->fail(SPHX_EINVAL, "bad profile arguments");
         RETCHK(sync_ctrl());
+        int rc = SPHX_OK;
+        by_lanes([&](auto t) {
+            rc = time_launches(reps, &ms[2], [&] { launch_neighbors<decltype(t)::value>(1, cur); });
+        });
+        RETCHK(rc);
         std::vector<Ctrl> saved(hctrl, hctrl + C);
         RETCHK(backup_state());
         for (int c = 0; c < C; ++c) {
@@ -1821,12 +1827,10 @@ struct Engine final : EngineBase {
             hctrl[c].midstep = 0;
             hctrl[c].err = 0;
         }
-        RETCHK(push_ctrl());
-        int rc_t = SPHX_OK;
-        by_lanes([&](auto t) { rc_t = profile_t<decltype(t)::value>(reps, ms); });
-        RETCHK(rc_t);
-        RETCHK(sync_ctrl());
-        int rc = first_error();
+        rc = push_ctrl();
+        if (rc == SPHX_OK) by_lanes([&](auto t) { rc = profile_t<decltype(t)::value>(reps, ms); });
+        if (rc == SPHX_OK) rc = sync_ctrl();
+        if (rc == SPHX_OK) rc = first_error();
         RETCHK(restore_state(saved));
         // the |v| slots the profiled launches filled
         HIPCHK(hipMemsetAsync(vslot, 0, sizeof(unsigned long long) * 2 * VSLOTS * C, s));
