@@ -152,6 +152,8 @@ template <typename real> struct KP {
     int fbase, nf, fcap;                      // fluid slots [fbase, fbase + fcap), the first nf used
     int wbase, nw;                            // wall slots [wbase, wbase + nw)
     int cbase, ncell;                         // cells [cbase, cbase + ncell), padding cell cbase + ncell
+    double sieve_scale;                       // unit of length of the 3D FP64 sieve: 1, or 1 / reach beyond FP32's range
+    float sieve_reach;                        // max(cell sizes, 2h) in that unit
 };
 
 // Neighbour lists are wave-tiled: the 64/T particles served by one
@@ -1177,8 +1179,10 @@ __global__ __launch_bounds__(TILE * TB) void k_neighbors(
 // place in the particle's list of hits in LDS. Its margin: rounding the
 // coordinates, |x_j|^2, the three multiply-adds and the threshold errs by less
 // than 34 * 2^-24 R^2, R the larger of |x_i| and |x_j|; for a pair within 2h
-// <= L, R^2 <= 2 (|x_i|^2 + L^2), so less than 4.1e-6 (|x_i|^2 + L^2); the
-// sieve allows 1e-5 (|x_i|^2 + L^2).
+// <= S, the largest of the cell sizes and 2h (a box may be smaller than 2h),
+// R^2 <= 2 (|x_i|^2 + S^2), so less than 4.1e-6 (|x_i|^2 + S^2); the sieve
+// allows 1e-5 (|x_i|^2 + S^2). Where S^2 would leave the range of FP32,
+// lengths are taken in units of S.
 //
 // Check: eight lanes per particle go through its hits, densely: the exact
 // predicate, the entry's cell offset, the kernel sum, and the compaction over
@@ -1224,6 +1228,10 @@ __global__ __launch_bounds__(64 * NB_WAVES) __attribute__((amdgpu_waves_per_eu(5
     __shared__ uint32_t hits[NB_WAVES][NB_UNIT][NB_HITS];
     __shared__ float4 unit[NB_WAVES][NB_UNIT];  // -2 x_i and the threshold
     __shared__ __align__(16) Axis axis[3];
+    // the sieve's unit of length, (2h)^2 and S^2 (in LDS:
+    // the kernel has no scalar register to spare, held there they cost 2 % at
+    // 2.0 M particles)
+    __shared__ __align__(16) struct { double scale; float rc2, slack; } sieve;
     const int b = xcd_block(blockIdx.x, gridDim.x);
     const KP<double>& P = Pt[tcase[b / NB_BLOCKS]];
     Ctrl* ctrl = ctrl_all + P.case_id;
@@ -1232,6 +1240,11 @@ __global__ __launch_bounds__(64 * NB_WAVES) __attribute__((amdgpu_waves_per_eu(5
         const int k = threadIdx.x;
         axis[k].half = P.periodic[k] ? P.half_period[k] : __longlong_as_double(0x7ff0000000000000ll);
         axis[k].period = P.period[k];
+    } else if (threadIdx.x == 3) {
+        const double u = P.sieve_scale;
+        sieve.scale = u;
+        sieve.rc2 = (float)(P.rc2 * u * u);
+        sieve.slack = P.sieve_reach * P.sieve_reach;
     }
     __syncthreads();
     if (ctrl->err) return;
@@ -1243,9 +1256,7 @@ __global__ __launch_bounds__(64 * NB_WAVES) __attribute__((amdgpu_waves_per_eu(5
     if (!__ballot(used)) return;
     const double xi[3] = {x0[i], x1[i], x2[i]};
     const G oi = geo[i];
-    const float Lm = (float)dmax(P.L[0], dmax(P.L[1], P.L[2]));
     const double rc2 = P.rc2;
-    const float rc2f = (float)rc2;
     const int kw = used ? cell[i] : 0;
     const int kc = kw & CELL_MASK;
     const int sb = (int)((uint32_t)kw >> CELL_BITS);
@@ -1296,10 +1307,11 @@ __global__ __launch_bounds__(64 * NB_WAVES) __attribute__((amdgpu_waves_per_eu(5
         // threshold nothing is below for those not in the group
         const double xr[3] = {lane_d(xi[0], f), lane_d(xi[1], f), lane_d(xi[2], f)};
         {
-            const float a0 = (float)(xi[0] - xr[0]), a1 = (float)(xi[1] - xr[1]),
-                        a2 = (float)(xi[2] - xr[2]);
+            const double u = sieve.scale;
+            const float a0 = (float)((xi[0] - xr[0]) * u), a1 = (float)((xi[1] - xr[1]) * u),
+                        a2 = (float)((xi[2] - xr[2]) * u);
             const float nn = a0 * a0 + a1 * a1 + a2 * a2;
-            const float t = mine ? rc2f + (1e-5f * (Lm * Lm + nn) - nn) : -__builtin_inff();
+            const float t = mine ? sieve.rc2 + (1e-5f * (sieve.slack + nn) - nn) : -__builtin_inff();
             if (c8 == 0) unit[wv][p] = float4{-2.f * a0, -2.f * a1, -2.f * a2, t};
             sync_lds();
         }
@@ -1359,7 +1371,8 @@ __global__ __launch_bounds__(64 * NB_WAVES) __attribute__((amdgpu_waves_per_eu(5
             }
             unsigned long long rows = __ballot(j1 > j0);
             if (!rows) continue;
-            const bool shifted = __ballot((tag >> 8) != 0 && j1 > j0);
+            // whether a candidate's offset needs more than a subtraction
+            const bool shifted = __ballot(((tag >> 8) != 0 || sieve.scale != 1.0) && j1 > j0);
 
             int cnt[NB_UNIT] = {};
             int fill = 0, img = 0;
@@ -1399,9 +1412,9 @@ __global__ __launch_bounds__(64 * NB_WAVES) __attribute__((amdgpu_waves_per_eu(5
                             const int m = (img >> (2 * k)) & 3;
                             return m == 1 ? d - axis[k].period : m == 2 ? d + axis[k].period : d;
                         };
-                        d0 = image(0, d0);
-                        d1 = image(1, d1);
-                        d2 = image(2, d2);
+                        d0 = image(0, d0) * sieve.scale;
+                        d1 = image(1, d1) * sieve.scale;
+                        d2 = image(2, d2) * sieve.scale;
                     }
                     float a0 = (float)d0, a1 = (float)d1, a2 = (float)d2;
                     float s2 = a0 * a0 + a1 * a1 + a2 * a2;

@@ -351,6 +351,10 @@ struct Engine final : EngineBase {
         // rows then lie 8 x-rows apart), plain row-major in 2D
         P.band = (D == 3 && P.n[1] > 8) ? 8 : P.n[1];
         P.rc2 = (2.0 * h) * (2.0 * h);
+        double reach = rc;
+        for (int k = 0; k < D; ++k) reach = std::max(reach, P.Ld[k]);
+        P.sieve_scale = reach > 1e-15 && reach < 1e15 ? 1.0 : 1.0 / reach;
+        P.sieve_reach = (float)(reach * P.sieve_scale);
         if (q.sigma0 > 0) {
             P.sigma0 = q.sigma0;
         } else {
