@@ -495,13 +495,14 @@ __global__ __launch_bounds__(256) void k_gnn_msg(int N, const int32_t* __restric
 // products and sums round and sum it, so the two agree bit for bit.
 
 // Rows N and N + 1 of a Q array: the learned vector that stands for Q_j at a
-// wall edge, and one so negative that its message is 0 (a tile row without an
-// edge). Edges then differ only in the row they read.
+// wall edge, and one of -inf, whose message relu(P_i - inf + R_e) is 0
+// whatever P_i and R_e hold, NaN included (a tile row without an edge). Edges
+// then differ only in the row they read.
 __device__ __forceinline__ void special_rows(float* __restrict__ Q, int N, const float* __restrict__ qw)
 {
     if (blockIdx.x != 0 || threadIdx.x >= HID) return;
     Q[(size_t)N * HID + threadIdx.x] = qw[threadIdx.x];
-    Q[(size_t)(N + 1) * HID + threadIdx.x] = -3e38f;
+    Q[(size_t)(N + 1) * HID + threadIdx.x] = -__builtin_inff();
 }
 
 // Node encoder H = relu(F Wn + bn), P = H Wa + bm, Q = H Wb of 16 nodes per
