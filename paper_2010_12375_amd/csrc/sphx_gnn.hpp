@@ -29,7 +29,7 @@ constexpr int HID = 64;
 constexpr int FPAD = 32;   // padded encoder input width
 constexpr int EFEAT = 8;   // edge features used
 constexpr int NOUT = 3;
-constexpr unsigned ROW_BYTES = HID * sizeof(float);  // of an FP32 row; row offsets are 32-bit
+constexpr unsigned ROW_BYTES = HID * sizeof(float);  // of an FP32 row
 constexpr int WALL_EDGE = -1;  // edst < 0: wall edge, wall index -1 - edst
 
 typedef __bf16 bf16;
@@ -148,6 +148,32 @@ __global__ __launch_bounds__(256) void k_gemm64(int M, const float* __restrict__
         }
     }
 }
+
+// The lane's column of a row of 64 floats, the row given by a uniform key. Up
+// to ROWS32 nodes the key is the row's byte offset and the row is read with a
+// buffer load, which takes the offset from a scalar register as it is; beyond
+// (BIG) offsets do not fit 32 bits: the key is the row's number and the
+// address a 64-bit product.
+constexpr int ROWS32 = (1 << 24) - 2;  // with the two special rows of Q
+template <bool BIG> struct Rows;
+template <> struct Rows<false> {
+    __amdgpu_buffer_rsrc_t p;
+    __device__ __forceinline__ Rows(const float* a, int n)
+        : p(__builtin_amdgcn_make_buffer_rsrc((void*)a, 0, (int)((unsigned)n * ROW_BYTES), 0x00020000))
+    {
+    }
+    static __host__ __device__ __forceinline__ int key(int row) { return (int)((unsigned)row * ROW_BYTES); }
+    __device__ __forceinline__ float at(int k, int lane) const
+    {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(p, lane * (int)sizeof(float), k, 0));
+    }
+};
+template <> struct Rows<true> {
+    const float* p;
+    __device__ __forceinline__ Rows(const float* a, int) : p(a) {}
+    static __host__ __device__ __forceinline__ int key(int row) { return row; }
+    __device__ __forceinline__ float at(int k, int lane) const { return p[(size_t)(unsigned)k * HID + lane]; }
+};
 
 // ---------------------------------------------------------------------
 // Weight gradient dW[KIN x 64] = X^T dZ over M rows, split over blocks of
@@ -384,12 +410,12 @@ __device__ __forceinline__ void edge_features(const FeatScale& c, float dx, floa
 // (2D).
 //
 // G rows hold `ldg` floats: EFEAT (the features alone) or FPAD (zero-padded,
-// for the unfused encoder product). esrc receives each edge's particle as the
-// byte offset of its row of 64 floats; the reverse edges (erev, for the
+// for the unfused encoder product). esrc receives the key (Rows) of the
+// row of each edge's particle; the reverse edges (erev, for the
 // backward of Q_j) are searched only when erev is given. (One thread per slot
 // left 3 200 wavefronts with a serial search each: 700 us at 205k nodes.)
 constexpr int EL = 8;
-template <typename real, int T>
+template <typename real, int T, bool BIG>
 __global__ __launch_bounds__(BLOCK) void k_gnn_edges(
     const KP<real>* __restrict__ Pt, const int32_t* __restrict__ tcase, int N, const int32_t* __restrict__ eoff,
     const uint32_t* __restrict__ nbr, const int32_t* __restrict__ ncnt, const uint32_t* __restrict__ wnb,
@@ -424,7 +450,7 @@ __global__ __launch_bounds__(BLOCK) void k_gnn_edges(
         gr[0] = make_float4(q[0], q[1], q[2], q[3]);
         gr[1] = make_float4(q[4], q[5], q[6], q[7]);
         for (int k = EFEAT / 4; k < ldg / 4; ++k) gr[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-        esrc[e] = (int)((unsigned)i * ROW_BYTES);
+        esrc[e] = Rows<BIG>::key(i);
     };
     for (int k = l; k < nin; k += EL) {
         const int e = e0 + k;
@@ -606,7 +632,7 @@ struct LayerKeep {
 // (173 scalar instructions a tile, 553 us). The node
 // update follows in the same block, on the rows it holds: wavefront w
 // computes output columns 16 w .. 16 w + 15.
-template <typename real, int NPW, bool TRAIN>
+template <typename real, int NPW, bool TRAIN, bool BIG>
 __global__ __launch_bounds__(256, 4) void k_gnn_layer(
     const KP<real>* __restrict__ Pt, const int32_t* __restrict__ tcase, int N, int lt,
     const uint32_t* __restrict__ nbr, const int32_t* __restrict__ ncnt, const uint32_t* __restrict__ wnb,
@@ -629,8 +655,7 @@ __global__ __launch_bounds__(256, 4) void k_gnn_layer(
     const int n0 = nb0 + wv * NPW;
     const KP<real>& P = Pt[tcase[nb0 / TILE]];
     if (W.WaT) special_rows(Qn, N, W.qn);
-    const __amdgpu_buffer_rsrc_t qrow =
-        __builtin_amdgcn_make_buffer_rsrc((void*)Qm, 0, (int)((unsigned)(N + 2) * ROW_BYTES), 0x00020000);
+    const Rows<BIG> qrow(Qm, N + 2);
     const FeatScale fs = feat_scale(P);
     const int maxn = P.maxn, maxw = P.maxw;
     const real L0 = P.L[0], L1 = P.L[1];
@@ -721,7 +746,7 @@ __global__ __launch_bounds__(256, 4) void k_gnn_layer(
                                 bf16_pair(f[6], f[7]));
             }
         }
-        dst = (int)((unsigned)dst * ROW_BYTES);
+        dst = Rows<BIG>::key(dst);
         *(uint4*)&Gs[wv][lane][0] = gq;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -732,8 +757,7 @@ __global__ __launch_bounds__(256, 4) void k_gnn_layer(
             float qv[16];
 #pragma unroll
             for (int row = 0; row < 16; ++row)
-                qv[row] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                    qrow, lane * (int)sizeof(float), __builtin_amdgcn_readlane(dst, 16 * t4 + row), 0));
+                qv[row] = qrow.at(__builtin_amdgcn_readlane(dst, 16 * t4 + row), lane);
             // E0^T = We^T G^T: lane (r, g) holds edge r, features 16 t + 4 g + q
             Frag gf;
             gf.q = make_uint4(0u, 0u, 0u, 0u);
@@ -881,19 +905,10 @@ __device__ __forceinline__ unsigned long long lane_word(unsigned long long v, in
     return ((unsigned long long)hi << 32) | lo;
 }
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const float* p, int N)
-{
-    return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)((unsigned)N * ROW_BYTES), 0x00020000);
-}
-// The lane's column of the row at byte offset `off` (uniform).
-__device__ __forceinline__ float row_load(__amdgpu_buffer_rsrc_t p, int off)
-{
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(p, (int)(threadIdx.x & 63) * 4, off, 0));
-}
-
 // Per node i (one wavefront, lane = feature): dP_i = sum_e dM_e,
 // wsum_i = sum over wall edges of dM_e (for qw), and dQ_i = sum of dM over the
 // inner edges that end at i, through the reverse of its own inner edges.
+template <bool BIG>
 __global__ __launch_bounds__(256) void k_gnn_node_bwd(int N, const int32_t* __restrict__ eoff,
                                                       const int32_t* __restrict__ edst,
                                                       const int32_t* __restrict__ erev,
@@ -904,7 +919,7 @@ __global__ __launch_bounds__(256) void k_gnn_node_bwd(int N, const int32_t* __re
     const int i = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (i >= N) return;
     const int lane = threadIdx.x & 63;
-    const __amdgpu_buffer_rsrc_t rows = rows_rsrc(dA, N);
+    const Rows<BIG> rows(dA, N);
     const float da = dA[(size_t)i * HID + lane];
     const int e0 = eoff[i], e1 = eoff[i + 1];
     float sp = 0.f, sw = 0.f, sq = 0.f;
@@ -918,7 +933,7 @@ __global__ __launch_bounds__(256) void k_gnn_node_bwd(int N, const int32_t* __re
             const int rv = erev[e];
             if (d >= 0 && rv >= 0) {
                 rev = mask[rv];
-                at = (int)((unsigned)d * ROW_BYTES);
+                at = Rows<BIG>::key(d);
             }
         }
         const unsigned long long wall = __ballot(d < 0);
@@ -926,7 +941,7 @@ __global__ __launch_bounds__(256) void k_gnn_node_bwd(int N, const int32_t* __re
         for (int k = 0; k < n; k += 8) {  // (words past n are 0)
             float dj[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) dj[u] = row_load(rows, __builtin_amdgcn_readlane(at, k + u));
+            for (int u = 0; u < 8; ++u) dj[u] = rows.at(__builtin_amdgcn_readlane(at, k + u), lane);
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const float dm = where_bit(lane_word(own, k + u), da);
@@ -946,6 +961,7 @@ __global__ __launch_bounds__(256) void k_gnn_node_bwd(int N, const int32_t* __re
 // registers and staged transposed (E0 from the matrix cores with the edges as
 // rows, so that a lane holds four consecutive edges of one feature; dM with
 // one lane per feature, its row of dA under the edge's sign word).
+template <bool BIG>
 __global__ __launch_bounds__(256) void k_gnn_wgrad_edge(int E, int rows, int N, const float* __restrict__ G,
                                                         const int32_t* __restrict__ esrc,
                                                         const uint16_t* __restrict__ WeT, const float* __restrict__ be,
@@ -956,7 +972,7 @@ __global__ __launch_bounds__(256) void k_gnn_wgrad_edge(int E, int rows, int N, 
     __shared__ __align__(16) uint16_t Zs[HID][WPAD];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int r = lane & 15, g = lane >> 4;
-    const __amdgpu_buffer_rsrc_t drow = rows_rsrc(dA, N);
+    const Rows<BIG> drow(dA, N);
     bf16x8 wef[4];
     float bev[4];
     f32x4 acc[4];
@@ -982,7 +998,7 @@ __global__ __launch_bounds__(256) void k_gnn_wgrad_edge(int E, int rows, int N, 
     for (int rb = r0; rb < r1; rb += WROWS) {
         float z[16];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) z[q] = row_load(drow, __builtin_amdgcn_readlane(at, q));
+        for (int q = 0; q < 16; ++q) z[q] = drow.at(__builtin_amdgcn_readlane(at, q), lane);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const f32x4 a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf, wef[t], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
@@ -1016,6 +1032,7 @@ struct EncBwd {
     const float* dA[3];
     const uint16_t* WcN[3];
 };
+template <bool BIG>
 __global__ __launch_bounds__(256) void k_gnn_enc_bwd(int E, int rows, int N, const float* __restrict__ G,
                                                      const int32_t* __restrict__ esrc,
                                                      const uint16_t* __restrict__ WeT, const float* __restrict__ be,
@@ -1070,10 +1087,10 @@ __global__ __launch_bounds__(256) void k_gnn_enc_bwd(int E, int rows, int N, con
 #pragma unroll
         for (int ll = 0; ll < 3; ++ll) {
             const int l = 2 - ll;
-            const __amdgpu_buffer_rsrc_t drow = rows_rsrc(B.dA[l], N);
+            const Rows<BIG> drow(B.dA[l], N);
             float z[16];
 #pragma unroll
-            for (int q = 0; q < 16; ++q) z[q] = row_load(drow, __builtin_amdgcn_readlane(at, q));
+            for (int q = 0; q < 16; ++q) z[q] = drow.at(__builtin_amdgcn_readlane(at, q), lane);
             if (ll) __syncthreads();  // the previous layer's rows have been read
 #pragma unroll
             for (int q = 0; q < 16; ++q)

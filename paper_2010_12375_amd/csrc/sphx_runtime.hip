@@ -2155,14 +2155,22 @@ struct Engine final : EngineBase {
         return SPHX_OK;
     }
 
+    // Call f with whether the nodes' rows need 64-bit offsets, as a constant.
+    template <typename F>
+    void by_rows(F&& f)
+    {
+        if (ntot > gnn::ROWS32) f(std::true_type{});
+        else f(std::false_type{});
+    }
+
     void launch_edges(bool unfused)
     {
         if constexpr (D == 2) {
-            by_lanes([&](auto t) {
-                gnn::k_gnn_edges<real, decltype(t)::value><<<nblk((long long)ntot * gnn::EL), BLOCK, 0, s>>>(
+            by_lanes([&](auto t) { by_rows([&](auto big) {
+                gnn::k_gnn_edges<real, decltype(t)::value, decltype(big)::value><<<nblk((long long)ntot * gnn::EL), BLOCK, 0, s>>>(
                     dP, tcase, ntot, gn.eoff, nbr, ncnt, wnb, wcnt, geo[cur], wgeo, st[cur], gn.edst,
                     unfused ? nullptr : gn.erev, gn.esrc, gn.G, unfused ? gnn::FPAD : gnn::EFEAT, gn.F);
-            });
+            }); });
         }
     }
 
@@ -2231,15 +2239,16 @@ struct Engine final : EngineBase {
         const float* Hi = train ? gn.X[l] : gn.Hs;
         float* Ho = train && !last ? gn.X[n] : gn.Hs;
         if constexpr (D == 2) {
-            auto go = [&](auto npw, auto tr) {
+            auto go = [&](auto npw, auto tr, auto big) {
                 constexpr int NPW = decltype(npw)::value;
-                gnn::k_gnn_layer<real, NPW, decltype(tr)::value><<<N / (4 * NPW), 256, 0, s>>>(
+                gnn::k_gnn_layer<real, NPW, decltype(tr)::value, decltype(big)::value><<<N / (4 * NPW), 256, 0, s>>>(
                     dP, tcase, N, lt, nbr, ncnt, wnb, wcnt, geo[cur], wgeo, st[cur], W, Hi, train ? 2 * H : H, Ho,
                     train && !last ? 2 * H : H, gn.P, gn.Q[l & 1], gn.Q[1 - (l & 1)], gn.Y, K);
             };
             auto width = [&](auto tr) {
-                if (N >= GNN_WIDE) go(std::integral_constant<int, 8>{}, tr);
-                else go(std::integral_constant<int, 4>{}, tr);
+                if (N > gnn::ROWS32) go(std::integral_constant<int, 8>{}, tr, std::true_type{});
+                else if (N >= GNN_WIDE) go(std::integral_constant<int, 8>{}, tr, std::false_type{});
+                else go(std::integral_constant<int, 4>{}, tr, std::false_type{});
             };
             if (train) width(std::true_type{});
             else width(std::false_type{});
@@ -2250,8 +2259,6 @@ struct Engine final : EngineBase {
     // The forward pass (with `train`, on the graph gnn_graph has made).
     int gnn_forward_impl(bool train)
     {
-        // rows are addressed with 32-bit byte offsets
-        if (ntot > (1 << 24) - 2) return ctx->fail(SPHX_ENOMEM, "too many particles for the surrogate");
         RETCHK(gnn_nodes(train));
         if (train) RETCHK(gnn_graph(false));
         const GnnLayout& L = gn.L;
@@ -2319,8 +2326,10 @@ struct Engine final : EngineBase {
             wgrad<128>(N, gn.X[l], 2 * H, gn.dZ, H, g + L.Wu[l], g + L.bu[l]);
             gemm<64, gnn::EPI_ACCUM>(N, gn.dZ, H, gn.wn + L.pWu[l], nullptr, gn.dH, H);
             gemm<64, gnn::EPI_STORE>(N, gn.dZ, H, gn.wn + L.pWu[l] + 64 * H, nullptr, gn.dA[l], H);
-            gnn::k_gnn_node_bwd<<<(N + 3) / 4, 256, 0, s>>>(N, gn.eoff, gn.edst, gn.erev, gn.mask[l], gn.dA[l], gn.dPb,
-                                                            gn.dQb, gn.wsum);
+            by_rows([&](auto big) {
+                gnn::k_gnn_node_bwd<decltype(big)::value><<<(N + 3) / 4, 256, 0, s>>>(
+                    N, gn.eoff, gn.edst, gn.erev, gn.mask[l], gn.dA[l], gn.dPb, gn.dQb, gn.wsum);
+            });
             {
                 const int rows = std::max(256, (N + PART_BLOCKS - 1) / PART_BLOCKS);
                 const int nb = (N + rows - 1) / rows;
@@ -2330,8 +2339,10 @@ struct Engine final : EngineBase {
             wgrad<64>(N, gn.X[l], 2 * H, gn.dPb, H, g + L.Wa[l], g + L.bm[l]);
             wgrad<64>(N, gn.X[l], 2 * H, gn.dQb, H, g + L.Wb[l], nullptr);
             if (E > 0) {
-                gnn::k_gnn_wgrad_edge<<<enb, 256, 0, s>>>((int)E, erows, N, gn.G, gn.esrc, gn.wt + L.pWe, p + L.be,
-                                                          gn.mask[l], gn.dA[l], gn.part);
+                by_rows([&](auto big) {
+                    gnn::k_gnn_wgrad_edge<decltype(big)::value><<<enb, 256, 0, s>>>(
+                        (int)E, erows, N, gn.G, gn.esrc, gn.wt + L.pWe, p + L.be, gn.mask[l], gn.dA[l], gn.part);
+                });
                 reduce_parts(enb, H * H, g + L.Wc[l]);
             }
             gemm<64, gnn::EPI_ACCUM>(N, gn.dPb, H, gn.wn + L.pWa[l], nullptr, gn.dH, H);
@@ -2342,8 +2353,10 @@ struct Engine final : EngineBase {
             const gnn::EncBwd B = {{gn.mask[0], gn.mask[1], gn.mask[2]},
                                    {gn.dA[0], gn.dA[1], gn.dA[2]},
                                    {gn.wn + L.pWc[0], gn.wn + L.pWc[1], gn.wn + L.pWc[2]}};
-            gnn::k_gnn_enc_bwd<<<enb, 256, 0, s>>>((int)E, erows, N, gn.G, gn.esrc, gn.wt + L.pWe, p + L.be, B, gn.part,
-                                                   gn.bpart);
+            by_rows([&](auto big) {
+                gnn::k_gnn_enc_bwd<decltype(big)::value><<<enb, 256, 0, s>>>(
+                    (int)E, erows, N, gn.G, gn.esrc, gn.wt + L.pWe, p + L.be, B, gn.part, gn.bpart);
+            });
             reduce_parts(enb, gnn::FPAD * H, g + L.We, H, g + L.be);
         }
         elem64(N, gn.dH, H, gn.X[0], 2 * H, gn.dZ, H);
