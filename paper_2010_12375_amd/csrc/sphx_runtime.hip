@@ -1046,8 +1046,11 @@ struct Engine final : EngineBase {
     template <int T>
     void launch_neighbors(int force, int b, int reinit = 0)
     {
-        // 3D with FP64 records: the wavefront-wide sieve (190 -> 88 us at 80 k
-        // particles; slower than k_neighbors in 2D and with FP32 records)
+        // 3D with FP64 records: the wavefront-wide sieve, at every size
+        // (k_neighbors without the kernel sums against it with them: 119 and
+        // 41 us at 500 particles, 103 and 39 at 9.5 k, 122 and 77 at 80 k,
+        // 243 and 186 at 250 k, 1550 and 1417 at 2.0 M); slower than
+        // k_neighbors in 2D and with FP32 records
         if constexpr (D == 3 && sizeof(real) == 8) {
             k_neighbors_wave<T><<<ntiles * NB_BLOCKS, 64 * NB_WAVES, 0, s>>>(
                 dP, tcase, ctrl, force, x[b][0], x[b][1], x[b][2], cell[b], fstart, geo[b], wx[0], wx[1], wx[2],
