@@ -203,7 +203,8 @@ int sphx_set_wall_velocity_case(sphx_ctx* ctx, int32_t c, const double* vel);
  * the storage of framework tensors; the caller keeps ownership and may free
  * the buffers when the call returns): the same arrays and meaning as
  * sphx_set_fluid_case, FP64, in original particle order. Before the batch's
- * first device layout the arrays are staged through the host. */
+ * first device layout, and where the case outgrows it, the arrays are staged
+ * through the host. */
 int sphx_set_fluid_device(sphx_ctx* ctx, int32_t c, int64_t n, const double* pos, const double* vel,
                           const double* rho, const double* drho);
 
@@ -326,7 +327,7 @@ int sphx_diagnostics_noalloc(sphx_ctx* ctx, int32_t c, sphx_diag* out);
 /* Average device time per launch (milliseconds) of the hot kernels,
  * measured with HIP events on the context's stream over `reps` launches
  * each, on the current state of every case (each case one acoustic sub-step
- * of its own dt_ac); state and clocks are restored afterwards. ms[0]
+ * of its own dt_ac); state, lists and clocks are as before afterwards. ms[0]
  * pressure relaxation, ms[1] density relaxation, ms[2] neighbour-list build,
  * ms[3] density re-initialisation. */
 int sphx_profile(sphx_ctx* ctx, int32_t reps, double* ms);
@@ -408,10 +409,10 @@ int sphx_gnn_train_step(sphx_ctx* ctx, double lr, double* loss);
  * products in one kernel, no edge array in device memory),
  * ms[1] the training graph's edge features, ms[2] the node update product by
  * itself, ms[3] one whole forward pass as inference runs it (features
- * included); for comparison the same with the edge
- * activations through device memory (the training forward's form): ms[4]
- * the whole pass, ms[5] its edge product R = E0 Wc, ms[6] its message sums
- * of one layer. sizes (may be NULL): [0] node rows, [1] edges. */
+ * included); for comparison the same forward by separate kernels, with the
+ * edge activations through device memory: ms[4] the whole pass, ms[5] its
+ * edge product R = E0 Wc, ms[6] its message sums of one layer. sizes (may be
+ * NULL): [0] node rows, [1] edges. */
 int sphx_gnn_profile(sphx_ctx* ctx, int32_t reps, double* ms, int64_t* sizes);
 
 /* `windows` surrogate windows: each predicts every case's mean rates over

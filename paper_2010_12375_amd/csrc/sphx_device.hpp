@@ -978,7 +978,10 @@ template <int B> struct BodyTag { static constexpr int value = B; };
 //
 // The kernel sum over the accepted neighbours is taken while they are found,
 // from the frozen offsets, and its density deviation is kept with the
-// configuration (dsum). With `reinit` (the update at the end of a queue), a
+// configuration (dsum), also where no step may follow: the build is 4 %
+// longer for it (3D, FP32, 250 k particles: 177 and 184 us), and a call that
+// does follow needs no build of its own (2.0 M particles, one build and one
+// step: 6.82 and 5.80 ms). With `reinit` (the update at the end of a queue), a
 // case whose next advection step has been prepared also gets that step's
 // density re-initialisation (Eq. eqrhosum / eqrhosumnosurface) here, saving a
 // launch.
@@ -1809,10 +1812,10 @@ __global__ __launch_bounds__(BLOCK) void k_adv_forces(
 }
 
 // ---------------------------------------------------------------------
-// Arithmetic of the pressure and density relaxations (S6, S7), shared by the
-// kernels that run them (one launch each, or all sub-steps of a queue in one
-// launch). Multiply-adds are written out and contraction is off, so that every
-// kernel computes the same bits whatever the compiler makes of the code around.
+// Arithmetic of the pressure and density relaxations (S6, S7), one function a
+// stage. Multiply-adds are written out and contraction is off, so that the
+// bits do not change with what the compiler makes of the code around (lane
+// counts, moving walls).
 
 // The particle's own quantities of a relaxation: velocity, rho - rho0 and
 // what follows from them.
@@ -2549,25 +2552,25 @@ __global__ __launch_bounds__(BLOCK) void k_vmax(const KP<real>* __restrict__ Pt,
 {
     const int lane = threadIdx.x & 63, w = wave_tile();
     const int t0 = w * VMAX_TILES, t1 = min(t0 + VMAX_TILES, ntiles);
-    real v2[VMAX_TILES];
-    // the tiles' squared speeds first, so that their loads are in flight together
+    real v[VMAX_TILES];
+    // the tiles' speeds first, so that their loads are in flight together
 #pragma unroll
     for (int k = 0; k < VMAX_TILES; ++k) {
-        v2[k] = 0;
+        v[k] = 0;
         if (t0 + k >= t1) continue;
         const KP<real>& P = Pt[tcase[t0 + k]];
         const int i = (t0 + k) * TILE + lane;
         if ((only >= 0 && P.case_id != only) || (mask && !mask[P.case_id]) || i >= P.fbase + P.nf) continue;
         const R4<real> s = st[i];
-        v2[k] = D == 2 ? sqrt(s.x * s.x + s.y * s.y) : sqrt(s.x * s.x + s.y * s.y + s.z * s.z);
+        v[k] = D == 2 ? sqrt(s.x * s.x + s.y * s.y) : sqrt(s.x * s.x + s.y * s.y + s.z * s.z);
     }
     double m = 0.0;
     bool nan = false;  // a tile of nothing but NaN
 #pragma unroll
     for (int k = 0; k < VMAX_TILES; ++k) {
         if (t0 + k >= t1) break;
-        m = fmax(m, (double)v2[k]);
-        nan = nan || __ballot(v2[k] == v2[k]) == 0ull;
+        m = fmax(m, (double)v[k]);
+        nan = nan || __ballot(v[k] == v[k]) == 0ull;
         if (k + 1 < VMAX_TILES && t0 + k + 1 < t1 && tcase[t0 + k + 1] == tcase[t0 + k]) continue;
         m = nan ? __builtin_nan("") : wave_max(m);
         if (lane == 0 && (nan || m > 0.0))

@@ -700,7 +700,9 @@ struct Engine final : EngineBase {
     }
 
     // Fluid from device memory (the context's device): staged on the host
-    // before the first device layout, copied device to device afterwards.
+    // before the first device layout and where the layout has to grow;
+    // otherwise read in place where a kernel can reach it, else copied device
+    // to device first (load_case).
     int set_fluid_device(int c, int64_t n, const double* pos, const double* vel, const double* rho,
                          const double* drho) override
     {
@@ -1144,13 +1146,12 @@ struct Engine final : EngineBase {
         return SPHX_OK;
     }
 
-    // One queue on set a (graph body): re-initialisation for the cases
-    // starting a step, the queued sub-steps, the step end (which prepares the
-    // next step or marks a continuation), the configuration update.
-    // One queue: the density re-initialisation (in 2D it came with the
-    // configuration update that ended the previous queue, or with advance's
-    // prologue) and the advection-step forces of the cases starting a step,
-    // the sub-steps, the configuration update.
+    // One queue on set a (graph body): the advection-step forces of the cases
+    // starting a step (its density re-initialisation came with the
+    // configuration update that ended the previous queue, or from the kept
+    // sums at advance's start), the queued sub-steps, the step end (which
+    // prepares the next step or marks a continuation), the configuration
+    // update.
     int enqueue_step(int a)
     {
         RETCHK(enqueue_adv_forces(1, a));
@@ -2443,9 +2444,12 @@ struct Engine final : EngineBase {
     }
 
     // Per-launch device time of the surrogate's kernels on the current
-    // configuration: ms[0] edge product R = E0 Wc, ms[1] message sums (one
-    // layer), ms[2] node update product [H | A] Wu, ms[3] a whole forward pass
-    // (graph and features included); sizes[0] nodes, sizes[1] edges.
+    // configuration: ms[0] one layer kernel, ms[1] the training graph's edge
+    // features, ms[2] the node update product [H | A] Wu by itself, ms[3] a
+    // whole forward pass; the forward by separate kernels with its edge
+    // activations through HBM: ms[4] the whole pass, ms[5] its edge product
+    // R = E0 Wc, ms[6] its message sums of one layer. sizes[0] nodes,
+    // sizes[1] edges.
     int gnn_profile(int32_t reps, double* ms, int64_t* sizes) override
     {
         RETCHK(gnn_check_ready());
