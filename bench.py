@@ -204,11 +204,14 @@ def surrogate_bench(args):
     gp = sim.gnn_profile(20)
     sim.close()
     E, N = gp["edges"], gp["nodes"]
-    # the fused layer: reads the edge features (8 FP32), the edge's two
-    # endpoints, P and Q once per node, writes A; the matrix cores do the edge
-    # encoder (K = 32, 8 of it features) and the edge product (K = 64)
-    fused_bytes = E * (8 * 4 + 8) + N * (4 + 3 * 64 * 4)
-    fused_flops = E * (2 * 32 * 64 + 2 * 64 * 64)
+    # one layer kernel, each value read and written once: a list word per
+    # edge; per node its two counts, frozen offsets, state record, P, Q and H,
+    # and H, P and Q of the next layer; the walls' offsets. Products: edge
+    # encoder (8 features) and edge product per edge, [H | A] Wu and the next
+    # P and Q per node
+    W = sum(c.n_wall for c in te)
+    fused_bytes = E * 4 + N * (8 + 8 + 16 + 6 * 64 * 4) + W * 8
+    fused_flops = E * (2 * 8 * 64 + 2 * 64 * 64) + N * (2 * 128 * 64 + 2 * 2 * 64 * 64)
     ms = gp["fused_layer"]
     t_hbm = fused_bytes / (HBM_PEAK_GBS * 1e9)
     t_mfma = fused_flops / (BF16_MFMA_TFLOPS * 1e12)
