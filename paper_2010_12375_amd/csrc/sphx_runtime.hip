@@ -2021,6 +2021,7 @@ struct Engine final : EngineBase {
         if (gn.Ncap >= N && gn.Ncap_train) return SPHX_OK;
         HIPCHK(hipStreamSynchronize(s));
         free_list(gn.nodes);
+        gn.Ncap = 0;  // nothing is held until every buffer is there
         auto& A = gn.nodes;
         const size_t n64 = (size_t)N * gnn::HID;
         RETCHK(dalloc(A, gn.ecount, N));
